@@ -11,11 +11,10 @@
 // launch shape. Nothing here is a dense contraction, so there is no MFMA: the
 // bound is HBM traffic (sparse pairs in, dense aggregate out, parameters in
 // and out).
+#include "frame.h"
 #include "marks.h"
 
 namespace scadles {
-
-typedef float f4 __attribute__((ext_vector_type(4)));
 
 // Range markers of every sparse device (one thread per range).
 __global__ __launch_bounds__(kBlock) void k_lb(AggArgs a, AggCtx c)
@@ -130,61 +129,63 @@ __device__ inline void load_batch(const AggArgs& a, uint32_t jb, uint32_t K, uin
   }
 }
 
-// Adds devices jb .. jb + kABatch - 1 in ascending order: the loaded first 64
-// entries, then any further entries in rounds of four 64-entry windows, or the
-// whole range of a dense device.
-__device__ inline void add_batch(const AggArgs& a, double* acc, uint32_t jb, uint32_t K, uint32_t eb, uint32_t em,
-                                 uint64_t dmask, uint64_t base, uint32_t len, const uint32_t (&ri)[kABatch],
-                                 const float (&rv)[kABatch])
+// A dense device's values of the range: lane l's two of every 128 positions.
+// (A device's gradient is only 4-byte aligned; 8-byte accesses need no more.)
+typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+constexpr int kADense = kARange / 128;
+
+__device__ inline void load_dense(f2 (&x)[kADense], const GLOBAL float* g, uint32_t len)
 {
   const uint32_t l = lane_id();
+  if (len == (uint32_t)kARange) {
 #pragma unroll
-  for (int jj = 0; jj < kABatch; ++jj) {
-    const uint32_t j = jb + jj;
-    if (j >= K) break;
-    const double w = (double)a.w[j];
-    if ((dmask >> j) & 1ull) {
-      const float* g = a.dense[j] + base;
-#pragma unroll 8
-      for (int m = 0; m < kARange / 64; ++m) {
-        const uint32_t e = m * 64 + l;
-        if (e < len) lds_add(&acc[e], w * (double)g[e]);
-      }
-      continue;
-    }
-    const uint32_t b = __builtin_amdgcn_readlane(eb, j);
-    const uint32_t m = __builtin_amdgcn_readlane(em, j);
-    if (l < m) add_entry(acc, ri[jj], rv[jj], base, w);
-    // Entries of one device hit distinct positions, so their order is free.
-    for (uint32_t o = 64; o < m; o += 256) {
-      uint32_t xi[4];
-      float xv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t q = o + u * 64 + l;
-        xi[u] = 0u;
-        xv[u] = 0.f;
-        if (q < m) {
-          xi[u] = a.idx[j][b + q];
-          xv[u] = a.val[j][b + q];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (o + u * 64 + l < m) add_entry(acc, xi[u], xv[u], base, w);
-    }
+    for (int m = 0; m < kADense; ++m) x[m] = *(const GLOBAL f2*)(g + m * 128 + 2 * l);
+    return;
   }
+#pragma unroll
+  for (int m = 0; m < kADense; ++m) {
+    const uint32_t e = m * 128 + 2 * l;
+    x[m].x = e < len ? g[e] : 0.f;
+    x[m].y = e + 1 < len ? g[e + 1] : 0.f;
+  }
+}
+
+// acc += w * x as plain LDS reads and writes: a wave's LDS operations execute
+// in program order, so these stay between the devices before and after.
+// Positions past the end of a short range add nothing anyone reads.
+__device__ inline void add_dense(double* acc, const f2 (&x)[kADense], double w)
+{
+  const uint32_t l = lane_id();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int m = 0; m < kADense; ++m) {
+    d2* p = reinterpret_cast<d2*>(acc + m * 128 + 2 * l);
+    d2 a = *p;
+    a.x = __builtin_fma(w, (double)x[m].x, a.x);
+    a.y = __builtin_fma(w, (double)x[m].y, a.y);
+    *p = a;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
 constexpr uint32_t kAGroup = 16;   // consecutive ranges per XCD turn
 
 // One wave per range. Lane j < K holds device j's entry interval [eb, eb + em)
 // in the range (from the range markers). Devices are added in ascending order,
-// kABatch at a time (see load_batch / add_batch). Dense devices add the whole
-// range from their gradient.
+// kABatch at a time (see load_batch). A dense device adds the whole range from
+// its gradient: the accumulators (16 KiB of LDS) leave ten waves to a compute
+// unit, too few to cover the memory's latency with 4-byte loads a few at a
+// time, so with kDense the next dense device's 8 KiB are in flight while the
+// sparse devices before it are added, and go into the accumulators as 16-byte
+// LDS reads and writes instead of 64-bit atomics (14 sparse and 2 dense sets
+// of 60.2 M: 531 -> 189 us; 8 sparse, 8 dense of 25.6 M within the step: 1424
+// -> 901 us). kDense is off where no dense device is expected (137 registers
+// against 92, 169 against 122 with momentum).
+template <bool kDense, bool kMom>
 __global__ __launch_bounds__(64) void k_aggregate(AggArgs a, AggCtx c)
 {
-  __shared__ double acc[kARange];
+  __shared__ __align__(16) double acc[kARange];
   const uint32_t l = threadIdx.x;
   const uint32_t K = c.K;
   // Workgroups are dealt to the GPU's 8 XCDs in turn; consecutive groups of
@@ -212,32 +213,80 @@ __global__ __launch_bounds__(64) void k_aggregate(AggArgs a, AggCtx c)
       em = e0 - b0;
     }
   }
-  const uint64_t dmask = ballot(dn);
+  uint64_t dmask = ballot(dn);
   // Parameters (and momentum buffer) of a full range are fetched now, used after the accumulation.
   f4 pp[kARange / 256], vv[kARange / 256];
   const bool pre = c.params && len == (uint32_t)kARange;
   if (pre) {
 #pragma unroll
     for (int m = 0; m < kARange / 256; ++m) pp[m] = *reinterpret_cast<const f4*>(c.params + base + m * 256 + l * 4);
-    if (c.mbuf) {
+    if (kMom) {
 #pragma unroll
       for (int m = 0; m < kARange / 256; ++m) vv[m] = *reinterpret_cast<const f4*>(c.mbuf + base + m * 256 + l * 4);
     }
   }
-#pragma unroll
-  for (int m = 0; m < kARange / 64; ++m) acc[m * 64 + l] = 0.0;
-
-  // Batches of kABatch devices, double-buffered: the next batch's loads are in
-  // flight while the current batch is added.
   uint32_t ia[kABatch], ib[kABatch];
   float va[kABatch], vb[kABatch];
   load_batch(a, 0, K, eb, em, ia, va);
+  // The next dense device, its whole range in flight while the sparse ones
+  // before it are added.
+  f2 xd[kADense];
+  uint32_t jd = kDense && dmask ? (uint32_t)__builtin_ctzll(dmask) : kMaxK;
+  if (jd < kMaxK) load_dense(xd, (const GLOBAL float*)a.dense[jd] + base, len);
+#pragma unroll
+  for (int m = 0; m < kARange / 128; ++m) *reinterpret_cast<d2*>(acc + m * 128 + 2 * l) = d2{0.0, 0.0};
+  // devices jb .. jb + kABatch - 1 in ascending order: the loaded first 64
+  // entries, then any further entries in rounds of four 64-entry windows
+  auto add_batch = [&](uint32_t jb, const uint32_t (&ri)[kABatch], const float (&rv)[kABatch]) {
+#pragma unroll
+    for (int jj = 0; jj < kABatch; ++jj) {
+      const uint32_t j = jb + jj;
+      if (j >= K) break;
+      const double w = (double)a.w[j];
+      if (kDense && j == jd) {
+        add_dense(acc, xd, w);
+        dmask &= dmask - 1;
+        jd = dmask ? (uint32_t)__builtin_ctzll(dmask) : kMaxK;
+        if (jd < kMaxK) load_dense(xd, (const GLOBAL float*)a.dense[jd] + base, len);
+        continue;
+      }
+      if (!kDense && ((dmask >> j) & 1ull)) {
+        // not expected (a device whose energies are not finite): no registers set aside
+        const GLOBAL float* g = (const GLOBAL float*)a.dense[j] + base;
+        for (uint32_t e = l; e < len; e += 64) lds_add(&acc[e], w * (double)g[e]);
+        continue;
+      }
+      const uint32_t b = __builtin_amdgcn_readlane(eb, j);
+      const uint32_t m = __builtin_amdgcn_readlane(em, j);
+      if (l < m) add_entry(acc, ri[jj], rv[jj], base, w);
+      // Entries of one device hit distinct positions, so their order is free.
+      for (uint32_t o = 64; o < m; o += 256) {
+        uint32_t xi[4];
+        float xv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t q = o + u * 64 + l;
+          xi[u] = 0u;
+          xv[u] = 0.f;
+          if (q < m) {
+            xi[u] = a.idx[j][b + q];
+            xv[u] = a.val[j][b + q];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (o + u * 64 + l < m) add_entry(acc, xi[u], xv[u], base, w);
+      }
+    }
+  };
+  // Batches of kABatch devices, double-buffered: the next batch's loads are in
+  // flight while the current batch is added.
   for (uint32_t jb = 0; jb < K; jb += 2 * kABatch) {
     if (jb + kABatch < K) load_batch(a, jb + kABatch, K, eb, em, ib, vb);
-    add_batch(a, acc, jb, K, eb, em, dmask, base, len, ia, va);
+    add_batch(jb, ia, va);
     if (jb + kABatch >= K) break;
     if (jb + 2 * kABatch < K) load_batch(a, jb + 2 * kABatch, K, eb, em, ia, va);
-    add_batch(a, acc, jb + kABatch, K, eb, em, dmask, base, len, ib, vb);
+    add_batch(jb + kABatch, ib, vb);
   }
 
   // Round once to float; optionally the SGD update of Eqn 4c (or momentum SGD
@@ -253,7 +302,7 @@ __global__ __launch_bounds__(64) void k_aggregate(AggArgs a, AggCtx c)
       const f4 g = {(float)acc[e], (float)acc[e + 1], (float)acc[e + 2], (float)acc[e + 3]};
       __builtin_nontemporal_store(g, reinterpret_cast<f4*>(c.out + base + e));
       f4 p = pp[m];
-      if (c.mbuf) {
+      if (kMom) {
         f4 v = vv[m];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -279,7 +328,7 @@ __global__ __launch_bounds__(64) void k_aggregate(AggArgs a, AggCtx c)
       __builtin_nontemporal_store(g, reinterpret_cast<f4*>(c.out + base + e));
       if (c.params) {
         f4 p = *reinterpret_cast<const f4*>(c.params + base + e);
-        if (c.mbuf) {
+        if (kMom) {
           f4 v = *reinterpret_cast<const f4*>(c.mbuf + base + e);
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -301,7 +350,7 @@ __global__ __launch_bounds__(64) void k_aggregate(AggArgs a, AggCtx c)
       for (uint32_t q = e; q < len; ++q) {
         const float g = (float)acc[q];
         c.out[base + q] = g;
-        if (c.params && c.mbuf) {
+        if (kMom && c.params) {
           float p = c.params[base + q], v = c.mbuf[base + q];
           momentum_step(p, v, g, nlr, mom, wd);
           c.mbuf[base + q] = v;
@@ -374,7 +423,13 @@ hipError_t launch_aggregate(const AggArgs& a, const AggCtx& c, uint32_t validate
       if (e != hipSuccess) return e;
     }
   }
-  k_aggregate<<<(c.nrange + 8 * kAGroup - 1) / (8 * kAGroup) * (8 * kAGroup), 64, 0, s>>>(a, c);
+  // Without dense devices (all sets sparse, or a rule that always sends Top-k)
+  // and without momentum the kernel needs fewer registers.
+  const dim3 grid((c.nrange + 8 * kAGroup - 1) / (8 * kAGroup) * (8 * kAGroup));
+  if (c.dense && c.mbuf) k_aggregate<true, true><<<grid, 64, 0, s>>>(a, c);
+  else if (c.dense) k_aggregate<true, false><<<grid, 64, 0, s>>>(a, c);
+  else if (c.mbuf) k_aggregate<false, true><<<grid, 64, 0, s>>>(a, c);
+  else k_aggregate<false, false><<<grid, 64, 0, s>>>(a, c);
   return hipGetLastError();
 }
 

@@ -967,6 +967,7 @@ scadles_status scadles_step_fused_layers(const float* const* grads, uint32_t K, 
   c.mom = opt.momentum;
   c.wd = opt.weight_decay;
   c.K = K;
+  c.dense = std::isinf(delta) ? 0u : 1u;   // +INFINITY always sends Top-k
   c.nrange = w.nrange;
   c.kmax = (uint32_t)kmax;
   c.n = n;
@@ -989,7 +990,7 @@ scadles_status scadles_weighted_aggregate(const scadles_sparse* sets, const floa
   AggArgs a;
   memset(&a, 0, sizeof(a));
   uint64_t kmax = 0;
-  uint32_t Kc = 0;
+  uint32_t Kc = 0, any_dense = 0;
   for (uint32_t j = 0; j < K; ++j) {
     const scadles_sparse& S = sets[j];
     if (S.k == 0) continue;
@@ -998,6 +999,7 @@ scadles_status scadles_weighted_aggregate(const scadles_sparse* sets, const floa
       if (S.k != n) return fail(SCADLES_EINVAL, "dense set %u must have k == n", j);
       if (!aligned(S.val, 4)) return fail(SCADLES_EINVAL, "dense set %u must be 4-byte aligned", j);
       a.dense[Kc] = S.val;
+      any_dense = 1;
     } else {
       if (S.k > n) return fail(SCADLES_EINVAL, "set %u has k = %llu > n", j, (unsigned long long)S.k);
       if (!aligned(S.idx, 4) || !aligned(S.val, 4)) return fail(SCADLES_EINVAL, "set %u is misaligned", j);
@@ -1020,6 +1022,7 @@ scadles_status scadles_weighted_aggregate(const scadles_sparse* sets, const floa
   c.err = reinterpret_cast<uint32_t*>(b + L.o_aerr);
   c.out = dense;
   c.K = Kc;
+  c.dense = any_dense;
   c.nrange = L.nrange;
   c.kmax = (uint32_t)kmax;
   c.n = n;
@@ -1144,6 +1147,7 @@ static scadles_status step_fused_impl(const float* const* grads, uint32_t K, uin
   c.mom = mom;
   c.wd = wd;
   c.K = K;
+  c.dense = std::isinf(delta) ? 0u : 1u;   // +INFINITY always sends Top-k
   c.nrange = L.nrange;
   c.kmax = (uint32_t)kmax;
   c.n = n;

@@ -20,7 +20,7 @@ constexpr int kSChunk = 256;           // contiguous sample chunk (1 KiB)
 constexpr int kBins = 2048;            // radix digit: 11 bits
 constexpr int kDigitBits = 11;
 constexpr int kARange = 2048;          // aggregation: positions per wave (16 KiB of doubles in LDS)
-constexpr int kABatch = 8;             // aggregation: devices whose entries are loaded together
+constexpr int kABatch = 8;             // aggregation: 64-entry windows loaded together
 constexpr int kMaxK = 64;              // SCADLES_MAX_DEVICES
 constexpr int kSlots = 4;              // selection slots per device
 constexpr int kSlotSampleLo = 0, kSlotSampleHi = 1, kSlotCand = 2, kSlotFull = 3;
@@ -171,6 +171,7 @@ struct AggCtx {
   uint32_t K;
   uint32_t nrange;        // ceil(n / kARange): waves of the aggregation kernel
   uint32_t kmax;
+  uint32_t dense;         // some device may contribute its dense gradient
   uint64_t n;
 };
 
