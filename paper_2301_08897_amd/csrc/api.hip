@@ -157,12 +157,13 @@ constexpr uint64_t kCapAlign = 64;
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
-  uint32_t K = 0, tpd = 0, nslot = 0, ngrp = 0, nfb = 0, nbmax = 0, nrange = 0, s_stride = 0, s_n = 0;
+  uint32_t K = 0, tpd = 0, nslot = 0, nseg = 0, nfb = 0, fb_rounds = 0, nrange = 0, s_stride = 0, s_n = 0;
   uint64_t n = 0;
-  uint32_t k[kMaxK], cap[kMaxK], mode[kMaxK], r_lo[kMaxK], r_hi[kMaxK];
+  uint32_t k[kMaxK], cap[kMaxK], seg[kMaxK], mode[kMaxK], r_lo[kMaxK], r_hi[kMaxK];
   uint32_t any_fast = 0;
-  size_t o_desc, o_st, o_hist, o_scnt, o_soff, o_olist, o_slot, o_epart, o_cidx, o_cval, o_band, o_gcnt, o_gpre, o_bcnt, o_bpre, o_be, o_fb, o_lb,
-      o_aerr;
+  uint64_t band_keys = 0;     // expected selection-interval keys of a device, the most
+  size_t o_desc, o_st, o_hist, o_lcnt, o_scnt, o_boff, o_hlist, o_tcnt, o_tpre, o_slot, o_epart, o_ekept, o_band,
+      o_lb, o_aerr;
   size_t total = 0;
 };
 
@@ -204,27 +205,35 @@ bool make_layout(uint32_t K, uint64_t n, const double* ratios, bool force_exact,
   // Tiles cover the 16-byte-aligned virtual row [0, n + shift), shift <= 3.
   L.tpd = ceil_div_u64(n + 3, kTile);
   L.nslot = L.tpd;
-  L.ngrp = ceil_div_u64(L.nslot, kGatherSlots);
+  // The tiles take the list segments and counters in turn: one per 64 tiles,
+  // up to kSegs, keeps the atomics on one address far enough apart.
+  L.nseg = std::min<uint32_t>(kSegs, std::max<uint32_t>(1u, L.nslot / 64));
   L.nrange = ceil_div_u64(n, kARange);
   sample_geometry(n, L.s_stride, L.s_n);
-  uint64_t sum_cap = 0;
+  uint64_t sum_band = 0;
   L.any_fast = 0;
   for (uint32_t j = 0; j < K; ++j) {
     const uint64_t k = with_select ? k_rule(n, ratios[j]) : 0;
     if (with_select && k == 0) return false;
     L.k[j] = (uint32_t)k;
-    L.cap[j] = 0;
+    L.cap[j] = L.seg[j] = 0;
     L.mode[j] = kModeExact;
     L.r_lo[j] = L.r_hi[j] = 0;
     if (!with_select) continue;
+    // Room for the selection-interval keys: the staged tiles' up to `cap`, the
+    // hot tiles' up to twice that for segments that fill unevenly. The interval
+    // of a random sample holds a fraction of the kept entries (12 standard
+    // deviations of the sample rank); what lies beyond goes to the exact path.
     uint64_t slack = n / 8;
     if (slack > (1ull << 20)) slack = 1ull << 20;
     uint64_t cap = 2 * k + slack;
     cap = (cap + kCapAlign - 1) / kCapAlign * kCapAlign;
+    const uint64_t seg = (2 * cap / L.nseg + kCapAlign - 1) / kCapAlign * kCapAlign;
     const bool fast = !force_exact && n >= kFastMinN && 2 * cap <= n && cap < (1ull << 31);
     if (fast) {
       L.mode[j] = kModeFast;
       L.cap[j] = (uint32_t)cap;
+      L.seg[j] = (uint32_t)seg;
       const double kf = (double)k * (double)L.s_n / (double)n;
       const double sd = std::sqrt(kf);
       double rlo = std::ceil(kf + 6.0 * sd + 8.0);
@@ -235,11 +244,16 @@ bool make_layout(uint32_t K, uint64_t n, const double* ratios, bool force_exact,
       L.r_lo[j] = (uint32_t)rlo;
       L.r_hi[j] = (uint32_t)rhi;
       L.any_fast = 1;
-      sum_cap += cap;
+      sum_band += seg * L.nseg + cap;
+      const double keys = (rlo - rhi) * (double)n / (double)L.s_n;
+      if (keys > (double)L.band_keys) L.band_keys = (uint64_t)keys;
     }
   }
-  L.nfb = ceil_div_u64(n + 3, kCBlk);
-  L.nbmax = L.nfb;
+  // Blocks of the exact path's histogram passes: 8 rounds, fewer where that
+  // leaves compute units without one.
+  L.fb_rounds = 8;
+  while (L.fb_rounds > 1 && (uint64_t)K * ceil_div_u64(n + 3, (uint64_t)L.fb_rounds * kRound) < 512) L.fb_rounds /= 2;
+  L.nfb = ceil_div_u64(n + 3, (uint64_t)L.fb_rounds * kRound);
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -250,22 +264,18 @@ bool make_layout(uint32_t K, uint64_t n, const double* ratios, bool force_exact,
     L.o_desc = take(sizeof(DevDesc) * K);
     L.o_st = take(sizeof(DevState) * K);
     L.o_hist = take(sizeof(uint32_t) * (size_t)K * kSlots * kBins);
+    L.o_lcnt = take(sizeof(uint64_t) * (size_t)K * kSegs);
+    const size_t tiles = (size_t)K * L.nslot;
+    L.o_scnt = take(sizeof(uint32_t) * tiles);
+    L.o_boff = take(sizeof(uint32_t) * tiles);
+    L.o_hlist = take(sizeof(uint32_t) * tiles);
+    L.o_tcnt = take(sizeof(uint32_t) * tiles);
+    L.o_tpre = take(sizeof(uint64_t) * tiles);
     // Slots are needed only by fast-path devices; sized for all K for simplicity.
-    const size_t nslots = L.any_fast ? (size_t)K * L.nslot : 0;
-    L.o_scnt = take(sizeof(uint32_t) * (size_t)K * L.nslot);
-    L.o_soff = take(sizeof(uint64_t) * (size_t)K * L.nslot);
-    L.o_olist = take(sizeof(uint32_t) * (size_t)K * L.nslot);
-    L.o_slot = take(sizeof(uint32_t) * nslots * kSlotWords);
-    L.o_epart = take(sizeof(double) * (size_t)K * L.nslot);
-    L.o_cidx = take(sizeof(uint32_t) * sum_cap);
-    L.o_cval = take(sizeof(float) * sum_cap);
-    L.o_band = take(sizeof(uint32_t) * sum_cap);
-    L.o_gcnt = take(sizeof(uint64_t) * (size_t)K * L.ngrp);
-    L.o_gpre = take(sizeof(uint64_t) * (size_t)K * L.ngrp);
-    L.o_bcnt = take(sizeof(uint64_t) * (size_t)K * L.nbmax);
-    L.o_bpre = take(sizeof(uint64_t) * (size_t)K * L.nbmax);
-    L.o_be = take(sizeof(double) * (size_t)K * L.nbmax);
-    L.o_fb = take(sizeof(uint32_t));
+    L.o_slot = take(sizeof(uint32_t) * (L.any_fast ? tiles : 0) * kSlotWords);
+    L.o_epart = take(sizeof(double) * tiles);
+    L.o_ekept = take(sizeof(double) * tiles);
+    L.o_band = take(sizeof(uint32_t) * sum_band);
   }
   L.o_lb = take(sizeof(uint32_t) * (size_t)K * L.nrange);
   L.o_aerr = take(256);
@@ -281,27 +291,23 @@ Ctx make_ctx(const Layout& L, void* ws)
   c.desc = reinterpret_cast<DevDesc*>(b + L.o_desc);
   c.st = reinterpret_cast<DevState*>(b + L.o_st);
   c.hist = reinterpret_cast<uint32_t*>(b + L.o_hist);
+  c.list_cnt = reinterpret_cast<unsigned long long*>(b + L.o_lcnt);
   c.slot_cnt = reinterpret_cast<uint32_t*>(b + L.o_scnt);
-  c.slot_off = reinterpret_cast<uint64_t*>(b + L.o_soff);
-  c.ovf_list = reinterpret_cast<uint32_t*>(b + L.o_olist);
+  c.slot_boff = reinterpret_cast<uint32_t*>(b + L.o_boff);
   c.slot = reinterpret_cast<uint32_t*>(b + L.o_slot);
+  c.hot_list = reinterpret_cast<uint32_t*>(b + L.o_hlist);
+  c.tile_cnt = reinterpret_cast<uint32_t*>(b + L.o_tcnt);
+  c.tile_pre = reinterpret_cast<uint64_t*>(b + L.o_tpre);
   c.epart = reinterpret_cast<double*>(b + L.o_epart);
-  c.cand_idx = reinterpret_cast<uint32_t*>(b + L.o_cidx);
-  c.cand_val = reinterpret_cast<float*>(b + L.o_cval);
+  c.ekept = reinterpret_cast<double*>(b + L.o_ekept);
   c.band = reinterpret_cast<uint32_t*>(b + L.o_band);
-  c.grp_cnt = reinterpret_cast<uint64_t*>(b + L.o_gcnt);
-  c.grp_pre = reinterpret_cast<uint64_t*>(b + L.o_gpre);
-  c.blk_cnt = reinterpret_cast<uint64_t*>(b + L.o_bcnt);
-  c.blk_pre = reinterpret_cast<uint64_t*>(b + L.o_bpre);
-  c.blk_e = reinterpret_cast<double*>(b + L.o_be);
-  c.fb_count = reinterpret_cast<uint32_t*>(b + L.o_fb);
   c.n = L.n;
   c.K = L.K;
   c.tpd = L.tpd;
   c.nslot = L.nslot;
-  c.ngrp = L.ngrp;
+  c.nseg = L.nseg;
   c.nfb = L.nfb;
-  c.nbmax = L.nbmax;
+  c.fb_rounds = L.fb_rounds;
   c.s_stride = L.s_stride;
   c.s_n = L.s_n;
   return c;
@@ -367,7 +373,10 @@ void select_setup(const Layout& L, void* ws, double delta, double* energies, uin
   p.any_fast = L.any_fast;
   p.sample_blocks = ceil_div_u64(L.s_n, kSBlk);
   const uint64_t tiles = (uint64_t)L.K * L.tpd;
-  p.full_workers = (uint32_t)(tiles < (uint64_t)kFullWorkers ? tiles : (uint64_t)kFullWorkers);
+  p.full_workers = (uint32_t)std::min<uint64_t>((uint64_t)L.K * L.nfb, kFullWorkers);
+  p.hot_workers = (uint32_t)std::min<uint64_t>(tiles, kHotWorkers);
+  // one workgroup per 2048 expected keys and one per segment's remainder
+  p.hist_blocks = (uint32_t)std::min<uint64_t>(L.band_keys / 2048 + L.nseg, 256);
   p.parts = parts_for(L);
   p.beside = 0;
   c.lb = lb;
@@ -470,6 +479,7 @@ static scadles_status topk_run(const float* grad, const Layout& L, uint32_t* idx
   a.val[0] = val;
   a.k[0] = L.k[0];
   a.cap[0] = L.cap[0];
+  a.seg[0] = L.seg[0];
   a.mode[0] = L.mode[0];
   a.r_lo[0] = L.r_lo[0];
   a.r_hi[0] = L.r_hi[0];
@@ -742,6 +752,7 @@ static scadles_status run_layers(const float* const* grads, uint32_t K, const ui
       a.val[j] = val[j] + at[(size_t)i * K + j];
       a.k[j] = Ll.k[j];
       a.cap[j] = Ll.cap[j];
+      a.seg[j] = Ll.seg[j];
       a.mode[j] = Ll.mode[j];
       a.r_lo[j] = Ll.r_lo[j];
       a.r_hi[j] = Ll.r_hi[j];
@@ -1122,6 +1133,7 @@ static scadles_status step_fused_impl(const float* const* grads, uint32_t K, uin
     a.val[j] = val[j];
     a.k[j] = L.k[j];
     a.cap[j] = L.cap[j];
+    a.seg[j] = L.seg[j];
     a.mode[j] = L.mode[j];
     a.r_lo[j] = L.r_lo[j];
     a.r_hi[j] = L.r_hi[j];

@@ -13,8 +13,6 @@ constexpr int kWaves = kBlock / 64;
 constexpr int kRound = kBlock * 4;     // elements per "round": one float4 per thread
 constexpr int kTile = 16384;           // main select pass: elements per workgroup (64 KiB)
 constexpr int kTileRounds = kTile / kRound;
-constexpr int kCBlk = 8192;            // candidate blocks (hist/compaction over candidates)
-constexpr int kCBlkRounds = kCBlk / kRound;
 constexpr int kSBlk = 4096;            // sample elements per workgroup
 constexpr int kSChunk = 256;           // contiguous sample chunk (1 KiB)
 constexpr int kBins = 2048;            // radix digit: 11 bits
@@ -22,16 +20,19 @@ constexpr int kDigitBits = 11;
 constexpr int kARange = 2048;          // aggregation: positions per wave (16 KiB of doubles in LDS)
 constexpr int kABatch = 8;             // aggregation: 64-entry windows loaded together
 constexpr int kMaxK = 64;              // SCADLES_MAX_DEVICES
-constexpr int kSlots = 4;              // selection slots per device
-constexpr int kSlotSampleLo = 0, kSlotSampleHi = 1, kSlotCand = 2, kSlotFull = 3;
+constexpr int kSlots = 3;              // selection slots per device: the bracket's two, the threshold's
+constexpr int kSlotSampleLo = 0, kSlotSampleHi = 1, kSlotSel = 2;
+constexpr int kSegs = 16;              // list segments of the hot tiles per device (at most: see Ctx::nseg)
+// Counters of workgroups done, per device (block_is_last): the sample passes,
+// the threshold's passes over the interval keys and over full data.
+constexpr int kTicketHist = 2, kTicketFull = 5, kTickets = 8;
 constexpr uint32_t kKeyInf = 0x80000000u;   // above every 31-bit key
 constexpr uint32_t kKeyMask = 0x7FFFFFFFu;
 constexpr uint64_t kSat31 = 0x7FFFFFFFull;
-constexpr int kFullWorkers = 1024;     // grid of the grid-stride exact-path kernels
+constexpr int kFullWorkers = 1024;     // grid-stride workgroups of the exact path's histogram passes
+constexpr int kHotWorkers = 4096;      // grid-stride workgroups for hot tiles
 constexpr int kWaveCap = 512;          // main pass: candidates one wave chunk (4096 elements) can stage
 constexpr int kSlotWords = 1024;       // 32-bit words of one tile's slot region (4 KiB)
-constexpr int kGatherSlots = 2;        // tiles per wave in the selection-list and output passes
-constexpr int kOverflowBlocks = 128;   // workgroups per device re-scanning overflowed tiles
 
 enum : uint32_t { kModeFast = 0, kModeExact = 1 };
 
@@ -50,9 +51,10 @@ struct DevDesc {          // per device, written once per call by the prep kerne
   const float* grad;
   uint32_t* idx_out;
   float* val_out;
-  uint64_t cand_off;      // first element of the device's candidate region
+  uint64_t band_off;      // first word of the device's selection-interval keys
   uint32_t k;
-  uint32_t cap;           // candidate capacity (0 in exact mode)
+  uint32_t seg_cap;       // words per list segment (0 in exact mode)
+  uint32_t list_cap;      // words of the gathered list
   uint32_t mode;
   uint32_t r_lo;          // sample ranks that bracket the k-th largest key
   uint32_t r_hi;          // 0: no upper bracket
@@ -76,15 +78,16 @@ struct Sel {
 
 struct DevState {
   Sel sel[kSlots];
-  uint64_t cand, sure;    // main pass totals: keys >= t_lo, keys >= t_hi
+  uint32_t ticket[kTickets];
   uint32_t t_lo, t_hi;    // bracket used by the main pass
-  uint32_t fallback;      // 1: the exact full-data path produces this device's output
+  uint32_t fallback;      // nonzero: the exact full-data path produces this device's output
   uint32_t thr;           // final threshold key (k-th largest)
   uint32_t err;           // internal error bits, kErr*
   uint64_t c_gt, need;    // keys above thr; keys equal to thr that are kept
   double e_all, e_kept;
   uint32_t sparse;        // 1: the device sends Top-k (adaptive rule), 0: dense
-  uint32_t ovf_n;         // entries in the device's ovf_list
+  uint32_t nhot;          // entries in the device's hot_list
+  unsigned long long gathered;  // keys appended to the gathered list | the staged tiles' keys >= t_hi << 32
 };
 
 // Kernel context: where everything lives in the workspace, plus call scalars.
@@ -92,35 +95,32 @@ struct Ctx {
   DevDesc* desc;
   DevState* st;
   uint32_t* hist;         // [K][kSlots][kBins]
-  uint32_t* slot_cnt;     // [K][nslot] per tile: candidates | overflowed << 15 | sure << 16
-  uint64_t* slot_off;     // [K][nslot] candidate | sure << 32 counts of the device's tiles before each tile
-  uint32_t* slot;         // [K][nslot][kSlotWords] per tile: candidates' value bits, then the keys of those
-                          // below t_hi; from the top down, the candidates' 16-bit offsets in the tile
-  uint32_t* ovf_list;     // [K][nslot] tiles with a wave chunk of more than kWaveCap candidates
-  double* epart;          // [K][nslot] sum of squares per tile, later kept sum of squares per write group
-  uint32_t* cand_idx;     // candidate regions (entries of overflowed slots only)
-  float* cand_val;
-  uint32_t* band;         // band lists: keys below t_hi of overflowed tiles, per device at cand_off
-  uint64_t* grp_cnt;      // [K][ngrp] kept-above | equal << 32 counts per write group of slots
-  uint64_t* grp_pre;      // [K][ngrp] exclusive prefix of grp_cnt
-  uint64_t* blk_cnt;      // [K][nbmax] packed (gt | eq << 32) per compaction block
-  uint64_t* blk_pre;      // [K][nbmax] exclusive prefix of blk_cnt
-  double* blk_e;          // [K][nbmax] kept sum of squares per compaction block
+  unsigned long long* list_cnt; // [K][kSegs] keys appended to a list segment | its tiles' keys >= t_hi << 32
+  uint32_t* slot_cnt;     // [K][nslot] per tile: candidates | hot << 15 | sure << 16
+  uint32_t* slot_boff;    // [K][nslot] where a hot tile's keys start in its list segment (tile % nseg)
+  uint32_t* slot;         // [K][nslot][kSlotWords] per tile: keys below t_hi, then the candidates' value bits;
+                          // from the top down, the candidates' 16-bit offsets in the tile (nothing for hot tiles)
+  uint32_t* hot_list;     // [K][nslot] tiles with more candidates than a wave stages or a slot holds
+  uint32_t* tile_cnt;     // [K][nslot] kept-above | equal << 16 counts per tile
+  uint64_t* tile_pre;     // [K][nslot] exclusive prefix of tile_cnt, kept-above | equal << 32
+  double* epart;          // [K][nslot] sum of squares per tile
+  double* ekept;          // [K][nslot] kept sum of squares per tile
+  uint32_t* band;         // keys in [t_lo, t_hi), per device: nseg segments of seg_cap words (hot tiles'),
+                          // then list_cap words (the staged tiles', gathered by the first radix pass)
   double* energies_out;   // caller's (dev, 2K) or null
   uint8_t* compressed_out;// caller's (dev, K) or null
   uint64_t n;
   uint32_t K;
   uint32_t tpd;           // main tiles per device: ceil((n + 3) / kTile)
   uint32_t nslot;         // slots (main-pass tiles) per device: tpd
-  uint32_t ngrp;          // write groups per device: ceil(nslot / kGatherSlots)
-  uint32_t nfb;           // exact-path blocks per device: ceil((n + 3) / kCBlk)
-  uint32_t nbmax;         // exact-path blocks allocated per device (nfb)
+  uint32_t nseg;          // list segments in use per device, at most kSegs
+  uint32_t fb_rounds;     // exact-path histogram blocks: rounds per block
+  uint32_t nfb;           // and blocks per device: ceil((n + 3) / (fb_rounds * kRound))
   uint32_t s_stride;      // sample chunk stride (elements)
   uint32_t s_n;           // sample elements per device
   uint32_t force_fallback;
   uint32_t inject_count_error;   // testing: device 0 reports kErrCount
   uint32_t j0, jn;        // devices [j0, j0 + jn) of this launch (the per-device kernels)
-  uint32_t* fb_count;     // devices on the exact path (the exact-path kernels exit early at 0)
   uint32_t* lb;           // fused step: aggregation range markers (see AggCtx), else null
   uint32_t nrange;
   double* ewma;           // [K][2] moving averages of E_all, E_kept (adaptive rule), or null
@@ -138,7 +138,8 @@ struct PrepArgs {
   uint32_t* idx[kMaxK];
   float* val[kMaxK];
   uint32_t k[kMaxK];
-  uint32_t cap[kMaxK];
+  uint32_t cap[kMaxK];    // words of the gathered list
+  uint32_t seg[kMaxK];    // words per list segment
   uint32_t mode[kMaxK];
   uint32_t r_lo[kMaxK];
   uint32_t r_hi[kMaxK];
@@ -180,7 +181,9 @@ constexpr uint32_t kMaxParts = 4;      // device groups whose main passes are pi
 struct SelectPlan {
   uint32_t any_fast;          // some device takes the sampled single-read path
   uint32_t sample_blocks;     // sample workgroups per device
-  uint32_t full_workers;      // grid-stride workgroups of the exact full-data path
+  uint32_t hist_blocks;       // workgroups per device of a threshold pass over the band list
+  uint32_t full_workers;      // grid-stride workgroups of the exact path's histogram passes
+  uint32_t hot_workers;       // grid-stride workgroups for hot tiles (all tiles of exact devices)
   uint32_t parts;             // device groups, 1 .. kMaxParts
   uint32_t beside;            // the rest runs beside other selections' main passes (small workgroups)
 };
