@@ -263,7 +263,7 @@ bool make_layout(uint32_t K, uint64_t n, const double* ratios, bool force_exact,
   if (with_select) {
     L.o_desc = take(sizeof(DevDesc) * K);
     L.o_st = take(sizeof(DevState) * K);
-    L.o_hist = take(sizeof(uint32_t) * (size_t)K * kSlots * kBins);
+    L.o_hist = take(sizeof(uint32_t) * (size_t)K * kSampleBins);
     L.o_lcnt = take(sizeof(uint64_t) * (size_t)K * kSegs);
     const size_t tiles = (size_t)K * L.nslot;
     L.o_scnt = take(sizeof(uint32_t) * tiles);
@@ -375,6 +375,7 @@ void select_setup(const Layout& L, void* ws, double delta, double* energies, uin
   const uint64_t tiles = (uint64_t)L.K * L.tpd;
   p.full_workers = (uint32_t)std::min<uint64_t>((uint64_t)L.K * L.nfb, kFullWorkers);
   p.hot_workers = (uint32_t)std::min<uint64_t>(tiles, kHotWorkers);
+  p.interval_keys = L.band_keys * L.K;
   // one workgroup per 2048 expected keys and one per segment's remainder
   p.hist_blocks = (uint32_t)std::min<uint64_t>(L.band_keys / 2048 + L.nseg, 256);
   p.parts = parts_for(L);

@@ -20,12 +20,12 @@ constexpr int kDigitBits = 11;
 constexpr int kARange = 2048;          // aggregation: positions per wave (16 KiB of doubles in LDS)
 constexpr int kABatch = 8;             // aggregation: 64-entry windows loaded together
 constexpr int kMaxK = 64;              // SCADLES_MAX_DEVICES
-constexpr int kSlots = 3;              // selection slots per device: the bracket's two, the threshold's
-constexpr int kSlotSampleLo = 0, kSlotSampleHi = 1, kSlotSel = 2;
+constexpr int kSampleBits = 13;        // top key bits (of 31) a lone pass over the sample tells apart
+constexpr int kSampleBins = 1 << kSampleBits;
 constexpr int kSegs = 16;              // list segments of the hot tiles per device (at most: see Ctx::nseg)
-// Counters of workgroups done, per device (block_is_last): the sample passes,
+// Counters of workgroups done, per device (block_is_last): the sample's passes,
 // the threshold's passes over the interval keys and over full data.
-constexpr int kTicketHist = 2, kTicketFull = 5, kTickets = 8;
+constexpr int kTicketSample = 0, kTicketRefine = 1, kTicketHist = 2, kTicketFull = 5, kTickets = 8;
 constexpr uint32_t kKeyInf = 0x80000000u;   // above every 31-bit key
 constexpr uint32_t kKeyMask = 0x7FFFFFFFu;
 constexpr uint64_t kSat31 = 0x7FFFFFFFull;
@@ -77,9 +77,11 @@ struct Sel {
 };
 
 struct DevState {
-  Sel sel[kSlots];
+  Sel sel;                // of the threshold
   uint32_t ticket[kTickets];
   uint32_t t_lo, t_hi;    // bracket used by the main pass
+  uint32_t bin_lo, bin_hi;      // two sample passes: the first one's bins and the ranks within them
+  uint32_t rank_lo, rank_hi;
   uint32_t fallback;      // nonzero: the exact full-data path produces this device's output
   uint32_t thr;           // final threshold key (k-th largest)
   uint32_t err;           // internal error bits, kErr*
@@ -94,7 +96,7 @@ struct DevState {
 struct Ctx {
   DevDesc* desc;
   DevState* st;
-  uint32_t* hist;         // [K][kSlots][kBins]
+  uint32_t* hist;         // [K][kSampleBins]; the threshold passes use the first kBins
   unsigned long long* list_cnt; // [K][kSegs] keys appended to a list segment | its tiles' keys >= t_hi << 32
   uint32_t* slot_cnt;     // [K][nslot] per tile: candidates | hot << 15 | sure << 16
   uint32_t* slot_boff;    // [K][nslot] where a hot tile's keys start in its list segment (tile % nseg)
@@ -181,6 +183,7 @@ constexpr uint32_t kMaxParts = 4;      // device groups whose main passes are pi
 struct SelectPlan {
   uint32_t any_fast;          // some device takes the sampled single-read path
   uint32_t sample_blocks;     // sample workgroups per device
+  uint64_t interval_keys;     // expected keys in [t_lo, t_hi) of all devices
   uint32_t hist_blocks;       // workgroups per device of a threshold pass over the band list
   uint32_t full_workers;      // grid-stride workgroups of the exact path's histogram passes
   uint32_t hot_workers;       // grid-stride workgroups for hot tiles (all tiles of exact devices)

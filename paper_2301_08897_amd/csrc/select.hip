@@ -7,9 +7,9 @@
 // finite values, so every decision below is exact integer work.
 //
 // Fast path (one read of every gradient, a second one of its hot tiles):
-//   1. bracket   : a systematic sample (256-element chunks at a fixed stride)
-//                  is radix-selected at two ranks around k * (sample/n), giving
-//                  keys t_lo <= (k-th largest key) < t_hi with high probability;
+//   1. bracket   : a histogram of a systematic sample (256-element chunks at a
+//                  fixed stride), at two ranks around k * (sample/n), gives keys
+//                  t_lo <= (k-th largest key) < t_hi with high probability;
 //   2. main pass : every gradient is read once; each tile stages its keys >=
 //                  t_lo (candidates) and those of them below t_hi (the selection
 //                  interval) in its slot in index order; sum g^2 is fused in. A
@@ -41,45 +41,30 @@ struct SelView {
   uint32_t lo, hi, shift, width, prefix;
 };
 
-// Width of the pending digit. The sample selections take 11-bit digits from
-// the top (their bracket stops after kBracketPasses digits); the exact
-// selections take the remainder bits first and 11-bit digits after, the same
-// number of passes with the smallest histogram in the first pass, which sees
+// Width of the pending digit: the remainder bits first and 11-bit digits after,
+// the fewest passes with the smallest histogram in the first one, which sees
 // the most keys and flushes the most bins.
-__device__ inline uint32_t digit_width(uint32_t bits, bool remainder_first)
+__device__ inline uint32_t digit_width(uint32_t bits)
 {
-  if (bits <= (uint32_t)kDigitBits) return bits;
-  if (!remainder_first) return (uint32_t)kDigitBits;
   const uint32_t r = bits % (uint32_t)kDigitBits;
   return r ? r : (uint32_t)kDigitBits;
 }
 
-__device__ inline SelView view_of(const Sel& s, bool remainder_first)
+__device__ inline SelView view_of(const Sel& s)
 {
   SelView v;
   v.lo = s.lo;
   v.hi = s.hi;
-  v.width = digit_width(s.bits, remainder_first);
+  v.width = digit_width(s.bits);
   v.shift = s.bits - v.width;
   v.prefix = s.prefix;
   return v;
 }
 
-// Digit of `key` for the pending pass, if the key is in the band and matches the
-// digits decided so far.
-__device__ inline bool sel_digit(const SelView& v, uint32_t key, uint32_t& d)
-{
-  if (key < v.lo || key >= v.hi) return false;
-  const uint32_t o = key - v.lo;
-  if ((o >> (v.shift + v.width)) != v.prefix) return false;
-  d = (o >> v.shift) & ((1u << v.width) - 1u);
-  return true;
-}
-
 // Threshold and ties kept.
 __device__ inline bool threshold_of(const DevState& s, uint32_t& thr, uint32_t& need)
 {
-  const Sel& sel = s.sel[kSlotSel];
+  const Sel& sel = s.sel;
   if (!sel.found) {
     thr = kKeyInf;
     need = 0;
@@ -88,6 +73,23 @@ __device__ inline bool threshold_of(const DevState& s, uint32_t& thr, uint32_t& 
   thr = sel.result;
   need = (uint32_t)sel.rank;
   return true;
+}
+
+// Counts the pending digit of every lane's key, where the key is in the band and
+// matches the digits decided so far, in an LDS histogram.
+// Lanes with the first such lane's digit are counted by one addition: equal
+// keys -- zeros, ties -- would otherwise queue on one bin.
+__device__ inline void count_digit(const SelView& v, uint32_t key, bool valid, uint32_t* h)
+{
+  const uint32_t o = key - v.lo;
+  const uint32_t d = (o >> v.shift) & ((1u << v.width) - 1u);
+  const bool in = valid & (key >= v.lo) & (key < v.hi) & ((o >> (v.shift + v.width)) == v.prefix);
+  const uint64_t m = ballot(in);
+  const uint32_t lead = m ? (uint32_t)__builtin_ctzll(m) : 0u;
+  const bool same = in & (d == (uint32_t)__builtin_amdgcn_readlane(d, lead));
+  const uint32_t n = (uint32_t)__builtin_popcountll(ballot(same));
+  const bool first = lane_id() == lead;
+  if (in & (!same | first)) atomicAdd(&h[d], first ? n : 1u);
 }
 
 __device__ inline void flush_hist(const uint32_t* h, uint32_t* g, int nb)
@@ -128,22 +130,21 @@ __device__ inline bool block_is_last(uint32_t* counter, uint32_t done, uint32_t 
 }
 
 // ---- block-wide rank selection over a histogram -----------------------------------------------
-// Among nb bins (nb a multiple of NT) holding counts of keys by digit, finds the
+// Among nb bins h(0) .. (nb a multiple of NT) holding counts of keys by digit, finds the
 // bin of the key of 1-based descending rank `rank` (the largest digit is the
 // top bin) and the number of keys in the bins above it. Every thread returns
 // the same result; false when rank exceeds the total.
 // The histogram must be complete (a barrier before the call); s_w holds
 // NT / 64 + 3 words of LDS.
-template <int NT>
-__device__ inline bool block_find(const uint32_t* h, int nb, uint64_t rank, uint32_t* s_w, uint32_t& bin,
-                                  uint64_t& above)
+template <int NT, class Bin>
+__device__ inline bool block_find(Bin h, int nb, uint64_t rank, uint32_t* s_w, uint32_t& bin, uint64_t& above)
 {
   constexpr int kW = NT / 64;
   const int per = nb / NT;
   const uint32_t tid = threadIdx.x, w = tid >> 6;
   const int b_hi = nb - (int)tid * per;               // this thread's bins [b_hi - per, b_hi), top first
   uint32_t sum = 0;
-  for (int i = 0; i < per; ++i) sum += h[b_hi - 1 - i];
+  for (int i = 0; i < per; ++i) sum += h(b_hi - 1 - i);
   const uint32_t incl = wave_incl_scan(sum);
   if (lane_id() == 63) s_w[w] = incl;
   if (tid == 0) s_w[kW + 2] = 0u;
@@ -153,7 +154,7 @@ __device__ inline bool block_find(const uint32_t* h, int nb, uint64_t rank, uint
   if (excl < rank && rank <= (uint64_t)excl + sum) {
     uint32_t cum = excl;
     for (int i = 0; i < per; ++i) {
-      const uint32_t v = h[b_hi - 1 - i];
+      const uint32_t v = h(b_hi - 1 - i);
       if ((uint64_t)cum + v >= rank) {
         s_w[kW] = (uint32_t)(b_hi - 1 - i);
         s_w[kW + 1] = cum;
@@ -171,27 +172,38 @@ __device__ inline bool block_find(const uint32_t* h, int nb, uint64_t rank, uint
   return ok;
 }
 
+// A complete histogram of N bins (device-scope sums of every workgroup) into LDS,
+// bin b at h[at(b)], and cleared for the next pass.
+template <int N, class At>
+__device__ inline void take_hist(uint32_t* g, uint32_t* h, At at)
+{
+  constexpr int kPer = N / kBlock, kOnce = kPer < 16 ? kPer : 16;
+  for (int i0 = 0; i0 < kPer; i0 += kOnce) {
+    uint32_t v[kOnce];
+#pragma unroll
+    for (int i = 0; i < kOnce; ++i) v[i] = get(g + (i0 + i) * kBlock + threadIdx.x);
+#pragma unroll
+    for (int i = 0; i < kOnce; ++i) {
+      const uint32_t b = (i0 + i) * kBlock + threadIdx.x;
+      h[at(b)] = v[i];
+      g[b] = 0u;
+    }
+  }
+}
+
 // Decides the pending digit of `sel` from its complete histogram g (device-scope
 // sums of every workgroup), which is cleared for the next pass. Called by all
 // threads of a workgroup, the same result in every thread. h: kBins words of
 // LDS, s_w: kWaves + 3. Returns false when the rank exceeds the keys counted.
-__device__ inline bool decide_digit(Sel& sel, uint32_t* g, uint32_t* h, uint32_t* s_w, bool remainder_first)
+__device__ inline bool decide_digit(Sel& sel, uint32_t* g, uint32_t* h, uint32_t* s_w)
 {
-  constexpr int kPer = kBins / kBlock;
-  uint32_t v[kPer];
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) v[i] = get(g + i * kBlock + threadIdx.x);
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    h[i * kBlock + threadIdx.x] = v[i];
-    g[i * kBlock + threadIdx.x] = 0u;
-  }
+  take_hist<kBins>(g, h, [](uint32_t b) { return b; });
   __syncthreads();
-  const uint32_t w = digit_width(sel.bits, remainder_first);
+  const uint32_t w = digit_width(sel.bits);
   const int nb = (1 << w) > kBlock ? 1 << w : kBlock;     // bins past the digit's are empty
   uint32_t bin;
   uint64_t above;
-  if (!block_find<kBlock>(h, nb, sel.rank, s_w, bin, above)) {
+  if (!block_find<kBlock>([&](int b) { return h[b]; }, nb, sel.rank, s_w, bin, above)) {
     sel.active = 0;
     sel.found = 0;
     return false;
@@ -206,33 +218,6 @@ __device__ inline bool decide_digit(Sel& sel, uint32_t* g, uint32_t* h, uint32_t
     sel.result = sel.lo + sel.prefix;
   }
   return true;
-}
-
-// Bracket of the main pass from the sample selections. The bracket only has to
-// be conservative (t_lo at or below the sample key of rank r_lo, t_hi above the
-// one of rank r_hi), so the selections stop after kBracketPasses digits: the
-// rank's bin [B, B + 2^bits) gives t_lo = B and t_hi = B + 2^bits. A selection
-// that missed gives t_lo = 0 (every key a candidate) or no upper bracket.
-constexpr int kBracketPasses = 2;
-
-__device__ inline void bracket_of(const DevDesc& d, const DevState& s, uint32_t& tlo, uint32_t& thi)
-{
-  if (d.mode != kModeFast) {
-    tlo = thi = kKeyInf;
-    return;
-  }
-  const Sel& a = s.sel[kSlotSampleLo];
-  const Sel& b = s.sel[kSlotSampleHi];
-  tlo = a.found ? a.result : (a.active ? a.lo + (a.prefix << a.bits) : 0u);
-  if (b.found) {
-    thi = b.result + 1u;
-  } else if (b.active) {
-    const uint64_t top = (uint64_t)b.lo + ((uint64_t)(b.prefix + 1u) << b.bits);
-    thi = top < (uint64_t)kKeyInf ? (uint32_t)top : kKeyInf;
-  } else {
-    thi = kKeyInf;
-  }
-  if (thi <= tlo) thi = kKeyInf;
 }
 
 // ---- 0. per-call preparation -----------------------------------------------------------------
@@ -260,98 +245,145 @@ __global__ __launch_bounds__(kBlock) void k_prep(Ctx c, PrepArgs a)
     __builtin_memset(&s, 0, sizeof(s));
     s.t_lo = s.t_hi = kKeyInf;
     s.thr = kKeyInf;
-    if (d.mode == kModeFast) {
-      Sel& lo = s.sel[kSlotSampleLo];
-      lo.active = 1;
-      lo.lo = 0;
-      lo.hi = kKeyInf;
-      lo.bits = 31;
-      lo.rank = d.r_lo;
-      if (d.r_hi >= 1) {
-        Sel& hi = s.sel[kSlotSampleHi];
-        hi.active = 1;
-        hi.lo = 0;
-        hi.hi = kKeyInf;
-        hi.bits = 31;
-        hi.rank = d.r_hi;
-      }
-    }
     c.st[j] = s;
   }
   if (blockIdx.x == 0)
     for (uint32_t i = threadIdx.x; i < K * kSegs; i += kBlock) c.list_cnt[i] = 0ull;
-  const uint64_t nh = (uint64_t)K * kSlots * kBins;
+  const uint64_t nh = (uint64_t)K * kSampleBins;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < nh; i += stride) c.hist[i] = 0u;
 }
 
-// ---- 1. bracket: histogram pass over the systematic sample (two selections) ----------------
-// The device's last workgroup decides the digit of both; in the last pass it
-// stores the bracket [t_lo, t_hi) for the main pass.
-__global__ __launch_bounds__(kBlock) void k_hist_sample(Ctx c, uint32_t pass)
+// ---- 1. bracket from the systematic sample ---------------------------------------------------
+// A histogram of the sample keys' top kBits bits. The bracket only has to be
+// conservative (t_lo at or below the sample key of rank r_lo, t_hi above the one
+// of rank r_hi), so a rank's bin [B, B + width) gives t_lo = B or t_hi = B +
+// width. Small selections stop after one pass of kSampleBits bits (bins of 3% of
+// the magnitude); for large ones, whose interval keys cost more than a
+// launch, a pass of kDigitBits bits is followed by one that tells apart
+// kRefineBits more within the two bins. The device's last workgroup finds the
+// bins and, in the last pass, stores the bracket for the main pass.
+constexpr int kRefineBits = 11;
+constexpr uint32_t kRefineBins = 1u << kRefineBits;
+
+// Sample elements e0 .. of the workgroup: four of every round per thread
+// (0 past the sample's end e1).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));    // four floats at any 4-byte address
+constexpr int kSampleRounds = kSBlk / kRound;
+
+__device__ inline void load_sample(const Ctx& c, const DevDesc& d, uint64_t e0, uint64_t e1, f4 (&x)[kSampleRounds])
 {
-  __shared__ uint32_t h[2][kBins];
-  __shared__ uint32_t s_w[kWaves + 3];
-  const uint32_t j = blockIdx.y;
-  const DevDesc& d = c.desc[j];
-  if (d.mode != kModeFast) return;
-  const Sel s0 = c.st[j].sel[kSlotSampleLo];
-  const Sel s1 = c.st[j].sel[kSlotSampleHi];
-  if (!s0.active && !s1.active) return;          // every workgroup of the device
-  const uint64_t e0 = (uint64_t)blockIdx.x * kSBlk;   // below s_n: the grid is ceil(s_n / kSBlk)
-  const SelView v0 = view_of(s0, false), v1 = view_of(s1, false);
-  // both selections at the same digit (always in the first pass): one histogram
-  const bool same = s0.active && s1.active && v0.lo == v1.lo && v0.hi == v1.hi && v0.shift == v1.shift &&
-                    v0.width == v1.width && v0.prefix == v1.prefix;
-  for (int b = threadIdx.x; b < 2 * kBins; b += kBlock) (&h[0][0])[b] = 0u;
-  constexpr int kR = kSBlk / kRound;
-  const uint64_t e1 = (e0 + kSBlk < c.s_n) ? e0 + kSBlk : c.s_n;
-  f4 x[kR];
 #pragma unroll
-  for (int r = 0; r < kR; ++r) {
+  for (int r = 0; r < kSampleRounds; ++r) {
     const uint64_t e = e0 + (uint64_t)r * kRound + threadIdx.x * 4;
     const uint64_t chunk = e / kSChunk, within = e % kSChunk;
     const uint64_t i = chunk * c.s_stride + within;     // real position of sample element e
-    if (d.shift == 0 && e + 4 <= e1) x[r] = ld4(d.grad + i);
+    if (e + 4 <= e1) x[r] = *(const GLOBAL f4u*)(gptr(d.grad) + i);
     else
       for (int q = 0; q < 4; ++q) x[r][q] = (e + q < e1) ? gptr(d.grad)[i + q] : 0.f;
   }
+}
+
+// The bracket from the bins of the two ranks (the upper rank 0: no upper bound).
+__device__ inline void store_bracket(DevState& st, const DevDesc& d, uint32_t lo, uint32_t hi, int shift, bool ok)
+{
+  // t_lo = 0: every key a candidate (a gradient of mostly zeros), more than the
+  // lists can hold, so the exact path takes the device from the start
+  if (!ok || lo == 0u) {
+    st.err |= kErrBracket;
+    return;                                       // t_lo = t_hi = kKeyInf from the preparation
+  }
+  st.t_lo = lo << shift;
+  st.t_hi = d.r_hi ? (hi + 1u) << shift : kKeyInf;
+}
+
+template <int kBits>
+__global__ __launch_bounds__(kBlock) void k_bracket(Ctx c, uint32_t refine)
+{
+  constexpr uint32_t kN = 1u << kBits;
+  constexpr int kShift = 31 - kBits;
+  __shared__ uint32_t h[kN + kN / 32];
+  __shared__ uint32_t s_w[kWaves + 3];
+  const uint32_t j = blockIdx.y, tid = threadIdx.x;
+  const DevDesc& d = c.desc[j];
+  if (d.mode != kModeFast) return;
+  const uint64_t e0 = (uint64_t)blockIdx.x * kSBlk;      // below s_n: the grid is ceil(s_n / kSBlk)
+  const uint64_t e1 = (e0 + kSBlk < c.s_n) ? e0 + kSBlk : c.s_n;
+  f4 x[kSampleRounds];
+  load_sample(c, d, e0, e1, x);
+  auto at = [](uint32_t b) { return b + (b >> 5); };     // spreads a thread's run of bins over the banks
+  for (uint32_t b = tid; b < kN + kN / 32; b += kBlock) h[b] = 0u;
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kR; ++r) {
-    const uint64_t e = e0 + (uint64_t)r * kRound + threadIdx.x * 4;
+  for (int r = 0; r < kSampleRounds; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (e0 + (uint64_t)r * kRound + tid * 4 + q < e1) atomicAdd(&h[at(key_of(x[r][q]) >> kShift)], 1u);
+  __syncthreads();
+  uint32_t* g = c.hist + (uint64_t)j * kSampleBins;
+  for (uint32_t b = tid; b < kN; b += kBlock) {
+    const uint32_t v = h[at(b)];
+    if (v) atomicAdd(g + b, v);
+  }
+  DevState& st = c.st[j];
+  if (!block_is_last(&st.ticket[kTicketSample], 1u, gridDim.x)) return;
+  take_hist<kN>(g, h, at);
+  __syncthreads();
+  auto bin_of = [&](int b) { return h[at((uint32_t)b)]; };
+  uint32_t lo, hi = 0;
+  uint64_t above_lo, above_hi = 0;
+  bool ok = block_find<kBlock>(bin_of, kN, d.r_lo, s_w, lo, above_lo);
+  if (d.r_hi) ok = block_find<kBlock>(bin_of, kN, d.r_hi, s_w, hi, above_hi) && ok;
+  if (tid != 0) return;
+  if (!refine) {
+    store_bracket(st, d, lo, hi, kShift, ok);
+    return;
+  }
+  if (!ok) st.err |= kErrBracket;
+  st.bin_lo = lo;
+  st.bin_hi = hi;
+  st.rank_lo = d.r_lo - (uint32_t)above_lo;
+  st.rank_hi = d.r_hi - (uint32_t)above_hi;
+}
+
+// The second pass: kRefineBits more bits of the sample keys in the two ranks' bins.
+__global__ __launch_bounds__(kBlock) void k_refine(Ctx c)
+{
+  constexpr int kShift = 31 - kDigitBits - kRefineBits;
+  __shared__ uint32_t h[2 * kRefineBins];
+  __shared__ uint32_t s_w[kWaves + 3];
+  const uint32_t j = blockIdx.y, tid = threadIdx.x;
+  const DevDesc& d = c.desc[j];
+  DevState& st = c.st[j];
+  if (d.mode != kModeFast || (st.err & kErrBracket)) return;
+  const uint64_t e0 = (uint64_t)blockIdx.x * kSBlk;
+  const uint64_t e1 = (e0 + kSBlk < c.s_n) ? e0 + kSBlk : c.s_n;
+  f4 x[kSampleRounds];
+  load_sample(c, d, e0, e1, x);
+  const uint32_t lo = st.bin_lo, hi = st.bin_hi;
+  for (uint32_t b = tid; b < 2 * kRefineBins; b += kBlock) h[b] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kSampleRounds; ++r)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (e + q >= e1) break;
-      const uint32_t key = key_of(x[r][q]);
-      uint32_t dg;
-      if (s0.active && sel_digit(v0, key, dg)) atomicAdd(&h[0][dg], 1u);
-      if (!same && s1.active && sel_digit(v1, key, dg)) atomicAdd(&h[1][dg], 1u);
+      if (e0 + (uint64_t)r * kRound + tid * 4 + q >= e1) break;
+      const uint32_t key = key_of(x[r][q]) >> kShift, bin = key >> kRefineBits;
+      if (bin == lo) atomicAdd(&h[key & (kRefineBins - 1)], 1u);
+      if (bin == hi) atomicAdd(&h[kRefineBins + (key & (kRefineBins - 1))], 1u);
     }
-  }
   __syncthreads();
-  if (s0.active) flush_hist(h[0], c.hist + ((uint64_t)j * kSlots + kSlotSampleLo) * kBins, kBins);
-  if (s1.active) flush_hist(same ? h[0] : h[1], c.hist + ((uint64_t)j * kSlots + kSlotSampleHi) * kBins, kBins);
-  DevState& st = c.st[j];
-  if (!block_is_last(&st.ticket[pass], 1u, gridDim.x)) return;
-  uint32_t err = st.err;
-  for (int s = kSlotSampleLo; s <= kSlotSampleHi; ++s) {
-    Sel sel = s == kSlotSampleLo ? s0 : s1;
-    if (!sel.active) continue;
-    // a miss sends the device to the exact path
-    if (!decide_digit(sel, c.hist + ((uint64_t)j * kSlots + s) * kBins, h[0], s_w, false)) err |= kErrBracket;
-    if (threadIdx.x == 0) st.sel[s] = sel;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    st.err = err;
-    if (pass + 1 == (uint32_t)kBracketPasses) {
-      uint32_t tlo, thi;
-      bracket_of(d, st, tlo, thi);
-      st.t_lo = tlo;
-      st.t_hi = thi;
-    }
-  }
+  uint32_t* g = c.hist + (uint64_t)j * kSampleBins;
+  flush_hist(h, g, 2 * kRefineBins);
+  if (!block_is_last(&st.ticket[kTicketRefine], 1u, gridDim.x)) return;
+  take_hist<2 * kRefineBins>(g, h, [](uint32_t b) { return b; });
+  __syncthreads();
+  uint32_t sub_lo, sub_hi = 0;
+  uint64_t above;
+  bool ok = block_find<kBlock>([&](int b) { return h[b]; }, kRefineBins, st.rank_lo, s_w, sub_lo, above);
+  if (d.r_hi) ok = block_find<kBlock>([&](int b) { return h[kRefineBins + b]; }, kRefineBins, st.rank_hi, s_w, sub_hi, above) && ok;
+  if (tid == 0)
+    store_bracket(st, d, (lo << kRefineBits) | sub_lo, (hi << kRefineBits) | sub_hi, kShift, ok);
 }
 
 // ---- 2. main pass: one read of every gradient ------------------------------------------------
@@ -685,13 +717,8 @@ __device__ inline void walk_slots(const Ctx& c, uint32_t j, uint32_t b, const De
   if (threadIdx.x == 0)
     s_n[kWaves] = (uint32_t)atomicAdd(&c.st[j].gathered,
                                       (unsigned long long)all | ((unsigned long long)((s_u[0] + s_u[1]) + (s_u[2] + s_u[3])) << 32));
-  auto add = [&](uint32_t key) {
-    uint32_t dg;
-    if (sel_digit(sv, key, dg)) atomicAdd(&h[dg], 1u);
-  };
 #pragma unroll
-  for (int i = 0; i < kBT; ++i)
-    if (l < (uint32_t)__builtin_amdgcn_readlane(nb, i)) add(kv[i]);
+  for (int i = 0; i < kBT; ++i) count_digit(sv, kv[i], l < (uint32_t)__builtin_amdgcn_readlane(nb, i), h);
   __syncthreads();
   uint32_t base = s_n[kWaves];
   // keys past the list's end are only counted: the device takes the exact path
@@ -710,11 +737,11 @@ __device__ inline void walk_slots(const Ctx& c, uint32_t j, uint32_t b, const De
 #pragma unroll
         for (int m = 0; m < 4; ++m) x[m] = e + m * 64 + l < n ? p[e + m * 64 + l] : 0u;
 #pragma unroll
-        for (int m = 0; m < 4; ++m)
-          if (e + m * 64 + l < n) {
-            if (room) dst[e + m * 64 + l] = x[m];
-            add(x[m]);
-          }
+        for (int m = 0; m < 4; ++m) {
+          const bool valid = e + m * 64 + l < n;
+          if (room && valid) dst[e + m * 64 + l] = x[m];
+          count_digit(sv, x[m], valid, h);
+        }
       }
     }
   }
@@ -737,14 +764,15 @@ __global__ __launch_bounds__(kBlock) void k_hist(Ctx c, uint32_t walk, uint32_t 
       sel = first_sel(st.t_lo, st.t_hi, 0);         // the rank follows from the counts
     } else {
       if (st.fallback) return;
-      sel = st.sel[kSlotSel];
+      sel = st.sel;
     }
     if (!sel.active) return;
     // lane i: segment i's keys (lane kSegs: the gathered list's), and its
     // chunks with those of the segments before
     const uint32_t l = lane_id();
     const uint64_t lc = l < (uint32_t)kSegs ? (uint64_t)c.list_cnt[(uint64_t)j * kSegs + l] : 0ull;
-    uint32_t cnt = (uint32_t)lc < d.seg_cap ? (uint32_t)lc : d.seg_cap;
+    const bool over = ballot((uint32_t)lc > d.seg_cap) != 0ull;      // in the first pass only
+    uint32_t cnt = over ? 0u : (uint32_t)lc;
     if (pass > 0 && l == (uint32_t)kSegs) cnt = (uint32_t)st.gathered;
     const uint32_t nch = (cnt + kHChunk - 1) / kHChunk;
     const uint32_t incl = wave_incl_scan(nch);
@@ -752,7 +780,7 @@ __global__ __launch_bounds__(kBlock) void k_hist(Ctx c, uint32_t walk, uint32_t 
     if (wb >= walk + items) return;
     for (int i = threadIdx.x; i < kBins; i += kBlock) h[i] = 0u;
     __syncthreads();
-    const SelView sv = view_of(sel, true);
+    const SelView sv = view_of(sel);
     if (wb < walk) {
       walk_slots<kBT>(c, j, wb, d, sv, h);
     } else {
@@ -769,29 +797,26 @@ __global__ __launch_bounds__(kBlock) void k_hist(Ctx c, uint32_t walk, uint32_t 
           key[r] = e < n ? p[e] : 0u;
         }
 #pragma unroll
-        for (int r = 0; r < (int)(kHChunk / kBlock); ++r) {
-          uint32_t dg;
-          if (e0 + r * kBlock < n && sel_digit(sv, key[r], dg)) atomicAdd(&h[dg], 1u);
-        }
+        for (int r = 0; r < (int)(kHChunk / kBlock); ++r) count_digit(sv, key[r], e0 + r * kBlock < n, h);
       }
     }
     __syncthreads();
-    uint32_t* g = c.hist + ((uint64_t)j * kSlots + kSlotSel) * kBins;
+    uint32_t* g = c.hist + (uint64_t)j * kSampleBins;
     flush_hist(h, g, kBins);
     if (!block_is_last(&st.ticket[kTicketHist + pass], 1u, walk + (items < per_dev ? items : per_dev))) return;
     bool exact = false;
     if (pass == 0) {
       const uint64_t staged = get(&st.gathered), hot = wave_sum_u64(lc);   // both halves count elements: no carry
       const uint64_t band = (uint64_t)(uint32_t)staged + (uint32_t)hot, sure = (staged >> 32) + (hot >> 32);
-      exact = ballot((uint32_t)lc > d.seg_cap) != 0ull || (uint32_t)staged > d.list_cap || band + sure < d.k ||
+      exact = over || (uint32_t)staged > d.list_cap || band + sure < d.k ||
               sure >= d.k;
       sel.rank = exact ? 1u : d.k - sure;
     }
-    const bool ok = decide_digit(sel, g, h, s_w, true);       // clears the histogram in any case
+    const bool ok = decide_digit(sel, g, h, s_w);       // clears the histogram in any case
     if (threadIdx.x == 0) {
       if (exact) st.fallback = kExactFound;
       else if (!ok) st.err |= kErrSelect;
-      st.sel[kSlotSel] = sel;
+      st.sel = sel;
     }
     return;
   }
@@ -809,13 +834,13 @@ __global__ __launch_bounds__(kBlock) void k_hist(Ctx c, uint32_t walk, uint32_t 
     if (!done) return;
     __syncthreads();
     DevState& st = c.st[cur];
-    uint32_t* g = c.hist + ((uint64_t)cur * kSlots + kSlotSel) * kBins;
+    uint32_t* g = c.hist + (uint64_t)cur * kSampleBins;
     flush_hist(h, g, kBins);
     if (block_is_last(&st.ticket[kTicketFull + own], done, c.nfb)) {
-      const bool ok = decide_digit(sel, g, h, s_w, true);
+      const bool ok = decide_digit(sel, g, h, s_w);
       if (threadIdx.x == 0) {
         if (!ok) st.err |= kErrSelect;
-        st.sel[kSlotSel] = sel;
+        st.sel = sel;
         if (pass == 0) st.fallback = kExactKnown;
       }
     }
@@ -829,24 +854,27 @@ __global__ __launch_bounds__(kBlock) void k_hist(Ctx c, uint32_t walk, uint32_t 
       close();
       cur = j;
       own = pass - (uint32_t)((behind >> jr) & 1ull);         // the device's pass
-      sel = own == 0 ? first_sel(0u, kKeyInf, c.desc[j].k) : c.st[j].sel[kSlotSel];
+      sel = own == 0 ? first_sel(0u, kKeyInf, c.desc[j].k) : c.st[j].sel;
       if (sel.active) {
         for (int i = threadIdx.x; i < kBins; i += kBlock) h[i] = 0u;
         __syncthreads();
-        sv = view_of(sel, true);
+        sv = view_of(sel);
         row = Row{gptr(c.desc[j].grad), c.desc[j].shift, c.n};
       }
     }
     if (!sel.active) continue;
     const uint64_t vbase = (uint64_t)blk * c.fb_rounds * kRound;
-#pragma unroll 4
-    for (uint32_t r = 0; r < c.fb_rounds; ++r) {
-      const uint64_t v = vbase + (uint64_t)r * kRound + threadIdx.x * 4;
-      const f4 x = load4(row, v, true);
+    for (uint32_t r0 = 0; r0 < c.fb_rounds; r0 += 4) {
+      f4 x[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        uint32_t dg;
-        if (in_row(row, v + e) && sel_digit(sv, key_of(x[e]), dg)) atomicAdd(&h[dg], 1u);
+      for (int r = 0; r < 4; ++r)
+        if (r0 + r < c.fb_rounds) x[r] = load4(row, vbase + (uint64_t)(r0 + r) * kRound + threadIdx.x * 4, true);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (r0 + r >= c.fb_rounds) break;
+        const uint64_t v = vbase + (uint64_t)(r0 + r) * kRound + threadIdx.x * 4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) count_digit(sv, key_of(x[r][e]), in_row(row, v + e), h);
       }
     }
     ++done;
@@ -1383,6 +1411,22 @@ static void launch_post(const Ctx& c, const SelectPlan& p, hipStream_t s, int ha
   k_final<<<c.jn, kBlock, 0, s>>>(c);
 }
 
+// One pass over the sample while the devices' expected interval keys are few:
+// its wider bins then cost less than a launch. (One / two passes, total: 4 x 1 M
+// 84 / 89 us, 8 x 11.2 M 195 / 195, one of 143.7 M 187 / 196, 16 x 60.2 M 1080 /
+// 1089 of which the threshold 95 / 78, 30 x 143.7 M 3537 / 3494.)
+static void launch_sample(const Ctx& c, const SelectPlan& p, hipStream_t s)
+{
+  if (!p.any_fast) return;
+  const dim3 grid(p.sample_blocks, c.K);
+  if (p.interval_keys < (1u << 19)) {
+    k_bracket<kSampleBits><<<grid, kBlock, 0, s>>>(c, 0u);
+    return;
+  }
+  k_bracket<kDigitBits><<<grid, kBlock, 0, s>>>(c, 1u);
+  k_refine<<<grid, kBlock, 0, s>>>(c);
+}
+
 // The whole selection. The devices are split into p.parts groups whose main
 // passes run one after the other on s. A main pass is bound by HBM bandwidth,
 // the threshold half of the rest of a group's selection by latency: that half
@@ -1400,14 +1444,11 @@ hipError_t launch_select(const Ctx& c0, const PrepArgs& a, const SelectPlan& p, 
   Ctx c = c0;
   c.j0 = 0;
   c.jn = c.K;
-  const uint64_t zero_words = (uint64_t)c.K * kSlots * kBins;
+  const uint64_t zero_words = (uint64_t)c.K * kSampleBins;
   uint32_t gprep = (uint32_t)((zero_words + kBlock * 8 - 1) / (kBlock * 8));
   gprep = gprep < 1 ? 1 : (gprep > 2048 ? 2048 : gprep);
   k_prep<<<gprep, kBlock, 0, s>>>(c, a);
-  if (p.any_fast) {
-    for (int pass = 0; pass < kBracketPasses; ++pass)
-      k_hist_sample<<<dim3(p.sample_blocks, c.K), kBlock, 0, s>>>(c, (uint32_t)pass);
-  }
+  launch_sample(c, p, s);
   if (ev) (void)hipEventRecord(ev[1], s);
   GradArgs ga;
   for (uint32_t j = 0; j < c.K; ++j) ga.grad[j] = a.grad[j];
@@ -1453,14 +1494,11 @@ hipError_t launch_bracket(const Ctx& c0, const PrepArgs& a, const SelectPlan& p,
   Ctx c = c0;
   c.j0 = 0;
   c.jn = c.K;
-  const uint64_t zero_words = (uint64_t)c.K * kSlots * kBins;
+  const uint64_t zero_words = (uint64_t)c.K * kSampleBins;
   uint32_t gprep = (uint32_t)((zero_words + kBlock * 8 - 1) / (kBlock * 8));
   gprep = gprep < 1 ? 1 : (gprep > 2048 ? 2048 : gprep);
   k_prep<<<gprep, kBlock, 0, s>>>(c, a);
-  if (p.any_fast) {
-    for (int pass = 0; pass < kBracketPasses; ++pass)
-      k_hist_sample<<<dim3(p.sample_blocks, c.K), kBlock, 0, s>>>(c, (uint32_t)pass);
-  }
+  launch_sample(c, p, s);
   return hipGetLastError();
 }
 
