@@ -381,12 +381,14 @@ const char* scadles_last_error(void);
  *                       overlaps the end of group i-1's selection, which runs
  *                       on a second stream the library creates per GPU, at the
  *                       default priority). Results do not depend on it.
- *   "row_max"        0..2^32-1 (default 2^21): in the per-layer selection,
- *                       layers of at most this many elements are selected as
- *                       (device, layer) rows; longer ones by the multi-launch
- *                       selection, consecutive ones pipelined on the library's
- *                       second stream and the rows on a third. Results do
- *                       not depend on it.
+ *   "row_max"        0..2^32-1: in the per-layer selection, layers of at most
+ *                       this many elements are selected as (device, layer)
+ *                       rows; longer ones by the multi-launch selection,
+ *                       consecutive ones pipelined on the library's second
+ *                       stream and the rows on a third. Until it is set:
+ *                       layers of up to 2^21 elements, and of up to 2^22 where
+ *                       their rows can be split (see row_split) and few enough
+ *                       entries are kept. Results do not depend on it.
  *   "row_split"      0..2^32-1 (default 65536, the least that takes effect):
  *                       rows of more than this many elements (and at most
  *                       2^24) are read by one workgroup per 16384-element part

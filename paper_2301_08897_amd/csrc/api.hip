@@ -38,8 +38,10 @@ scadles_status fail(scadles_status st, const char* fmt, ...)
 namespace {
 
 std::atomic<int> g_validate{0}, g_force_exact{0}, g_force_fallback{0}, g_parts{1}, g_inject_count_error{0};
-// per-layer selection: layers of at most this many elements go to the row kernels
-std::atomic<int64_t> g_row_max{1 << 21};
+// per-layer selection: layers of at most this many elements go to the row
+// kernels; kRowMaxAuto: by row_layer's rule
+constexpr int64_t kRowMaxAuto = -1;
+std::atomic<int64_t> g_row_max{kRowMaxAuto};
 std::atomic<int64_t> g_row_split{65536};
 std::atomic<int64_t> g_layer_order{1};
 // Per-layer selection: workspace regions of the long layers, used in turn; the
@@ -577,6 +579,27 @@ static uint64_t row_cand_list(uint64_t n, const double* ratios, uint32_t K)
   return row_parts_of(n) * kRowPartWaves * row_wave_cap(n, ratios, K);
 }
 
+// Whether a layer of n elements is selected as rows. Without the option: up to
+// 2^21 elements, and up to 2^22 while it can be split and its select workgroup
+// has room for the selection interval (12 standard deviations of the sample rank
+// and 16 ranks; a tenth for chance). A split row costs no launches of its own
+// (16 x 143.7 M with four layers of 2 to 4 M: 2620 us by the multi-launch
+// selection, 2393 as rows), but one whose interval does not fit after all, as
+// with mostly zeros, is selected by a single workgroup, whose time grows with
+// the row: hence the bound (8 devices x 8 layers of 7.5 M: 1173 and 772 us, but
+// a row of 9.6 M that did not fit 8 ms).
+static bool row_layer(uint64_t n, const double* ratios, uint32_t K)
+{
+  const int64_t most = g_row_max.load();
+  if (most != kRowMaxAuto) return n <= (uint64_t)most;
+  if (n <= (1u << 21)) return true;
+  if (n > (1u << 22) || row_cand_list(n, ratios, K) == 0) return false;
+  uint64_t kmax = 0;
+  for (uint32_t j = 0; j < K; ++j) kmax = std::max<uint64_t>(kmax, k_rule(n, ratios[j]));
+  const double sample_k = (double)kmax / kRowSampleEvery;
+  return 1.1 * kRowSampleEvery * (12.0 * std::sqrt(sample_k) + 16.0) <= (double)kRowBigCand;
+}
+
 static LayersWs layers_ws(uint32_t K, const uint64_t* seg_off, uint32_t L, const double* ratios)
 {
   LayersWs w;
@@ -628,12 +651,14 @@ static scadles_status run_layers(const float* const* grads, uint32_t K, const ui
 {
   uint8_t* base = static_cast<uint8_t*>(ws);
 
-  // Short layers (at most row_max elements), longest first, go to the row
-  // kernels: one workgroup per (layer, device) row, all in one launch.
-  const uint64_t row_max = (uint64_t)g_row_max.load();
+  // Short layers, longest first, go to the row kernels: one workgroup per
+  // (layer, device) row, all in one launch.
   std::vector<uint32_t> shorts;
-  for (uint32_t l = 0; l < L; ++l)
-    if (seg_off[l + 1] - seg_off[l] <= row_max) shorts.push_back(l);
+  std::vector<uint8_t> is_row(L);
+  for (uint32_t l = 0; l < L; ++l) {
+    is_row[l] = row_layer(seg_off[l + 1] - seg_off[l], ratios, K);
+    if (is_row[l]) shorts.push_back(l);
+  }
   std::stable_sort(shorts.begin(), shorts.end(), [&](uint32_t a, uint32_t b) {
     return seg_off[a + 1] - seg_off[a] > seg_off[b + 1] - seg_off[b];
   });
@@ -723,7 +748,7 @@ static scadles_status run_layers(const float* const* grads, uint32_t K, const ui
     uint64_t run[kMaxK] = {};
     for (uint32_t l = 0; l < L; ++l) {
       const uint64_t nl = seg_off[l + 1] - seg_off[l];
-      if (nl > row_max) {
+      if (!is_row[l]) {
         layer.push_back(l);
         at.insert(at.end(), run, run + K);
       }
@@ -763,6 +788,13 @@ static scadles_status run_layers(const float* const* grads, uint32_t K, const ui
                  nullptr, nullptr, nullptr, (uint32_t)off, 2u * L, ll.c, ll.p);
     ll.p.parts = 1;
     ll.p.beside = 1;
+    // few persistent workgroups: each waits for a slot the main pass leaves.
+    // Where most tiles will be hot (their slots hold 4% of the elements) theirs
+    // is the most of the work, and it takes as many as ever.
+    uint64_t kmax = 0;
+    for (uint32_t j = 0; j < K; ++j) kmax = std::max<uint64_t>(kmax, Ll.k[j]);
+    if (kmax < nl / 32) ll.p.hot_workers = std::min<uint32_t>(ll.p.hot_workers, kBesideWorkers);
+    ll.p.full_workers = std::min<uint32_t>(ll.p.full_workers, kBesideWorkers);
     ll.c.err_acc = err_acc;
   }
 
@@ -787,9 +819,7 @@ static scadles_status run_layers(const float* const* grads, uint32_t K, const ui
     if (e == hipSuccess) e = hipStreamWaitEvent(sr, ss->fork, 0);
     if (e != hipSuccess) return hip_fail(e, "row stream fork");
   }
-  e = launch_put_table(table.data(), table.size(), reinterpret_cast<uint64_t*>(base + lw.table), sr);
-  if (e != hipSuccess) return hip_fail(e, "layer table");
-  e = launch_rows(rc, rp, any_long ? nullptr : energies, sr);
+  e = launch_rows(rc, rp, table.data(), table.size(), any_long ? nullptr : energies, sr);
   if (e != hipSuccess) return hip_fail(e, "row selection");
   if (rows_beside) {
     e = hipEventRecord(ss->rows_done, sr);

@@ -116,18 +116,24 @@ __global__ __launch_bounds__(256) void k_put(PutArgs a)
 // One workgroup per device: every layer's k (the same rule as the host's),
 // the exclusive prefix of k over the layers (where the layer's entries start
 // in the device's output), and the row descriptors of the short layers.
-__global__ __launch_bounds__(256) void k_rows_prep(RowsCtx rc, RowsPrep rp)
+// A table of up to kPutWords words comes with the kernel arguments (put.count):
+// the first workgroup copies it for the later launches. Longer ones were
+// copied before (k_put).
+__global__ __launch_bounds__(256) void k_rows_prep(RowsCtx rc, RowsPrep rp, PutArgs put)
 {
   __shared__ uint64_t s_w[4];
   const uint32_t j = blockIdx.x, tid = threadIdx.x;
+  const uint64_t* table = put.count ? put.v : rc.table;
+  if (j == 0)
+    for (uint32_t i = tid; i < put.count; i += 256) put.dst[i] = put.v[i];
   const double ratio = rp.ratio[j];
   uint64_t run = 0;
   for (uint32_t l0 = 0; l0 < rc.L; l0 += 256) {
     const uint32_t l = l0 + tid;
     uint64_t off = 0, nl = 0, kl = 0;
     if (l < rc.L) {
-      off = rc.table[l];
-      nl = rc.table[l + 1] - off;
+      off = table[l];
+      nl = table[l + 1] - off;
       kl = k_of(nl, ratio);
     }
     uint64_t incl = kl;
@@ -143,7 +149,7 @@ __global__ __launch_bounds__(256) void k_rows_prep(RowsCtx rc, RowsPrep rp)
     const uint64_t chunk = s_w[0] + s_w[1] + s_w[2] + s_w[3];
     __syncthreads();
     if (l < rc.L) {
-      const uint64_t q = rc.table[rc.L + 1 + l];
+      const uint64_t q = table[rc.L + 1 + l];
       if (q != kNotShort) {
         RowDesc d;
         d.grad = rp.grad[j] + off;
@@ -303,8 +309,12 @@ __device__ inline uint32_t row_select_global(const Row& row, uint64_t vend, uint
 // chunks every kRowSampleStride elements; the whole row when it is short):
 // the bins of its 13-bit histogram (in shist, kRowCand words of LDS) around
 // k's expected sample rank, six standard deviations and 8 ranks either side.
-__device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t vend, uint32_t* shist, uint32_t* s_w,
-                                   uint32_t* s_res, uint32_t& t_lo, uint32_t& t_hi)
+// With `refine` a second pass over the sample tells apart kRowRefineBits more
+// bits within the two bins: a long row's bins of 3% of the magnitude may hold
+// more keys than its select workgroup has room for.
+constexpr int kRowRefineBits = 11;
+__device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t vend, bool refine, uint32_t* shist,
+                                   uint32_t* s_w, uint32_t* s_res, uint32_t& t_lo, uint32_t& t_hi)
 {
   static_assert((1 << kRowSampleBits) <= kRowCand, "the sample histogram fits the candidate array");
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
@@ -312,26 +322,30 @@ __device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t ve
   const uint64_t stride = whole ? 256u : (uint64_t)kRowSampleStride;
   for (uint32_t i = tid; i < (1u << kRowSampleBits); i += kRowBlock) shist[i] = 0u;
   __syncthreads();
-  uint32_t s_cnt = 0;
-  for (uint64_t c0 = w; c0 * stride < vend; c0 += 4 * kRowWaves) {
-    f4 x[4];
+  // visit(key) for the calling thread's keys of the sample
+  auto sample = [&](auto visit) {
+    for (uint64_t c0 = w; c0 * stride < vend; c0 += 4 * kRowWaves) {
+      f4 x[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const uint64_t v = (c0 + r * kRowWaves) * stride + 4u * lane;
-      x[r] = v < vend ? load4(row, v, false) : f4{0.f, 0.f, 0.f, 0.f};
-    }
+      for (int r = 0; r < 4; ++r) {
+        const uint64_t v = (c0 + r * kRowWaves) * stride + 4u * lane;
+        x[r] = v < vend ? load4(row, v, false) : f4{0.f, 0.f, 0.f, 0.f};
+      }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const uint64_t v = (c0 + r * kRowWaves) * stride + 4u * lane;
+      for (int r = 0; r < 4; ++r) {
+        const uint64_t v = (c0 + r * kRowWaves) * stride + 4u * lane;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (v < vend && in_row(row, v + q)) {
-          atomicAdd(&shist[key_of(x[r][q]) >> (31 - kRowSampleBits)], 1u);
-          ++s_cnt;
-        }
+        for (int q = 0; q < 4; ++q)
+          if (v < vend && in_row(row, v + q)) visit(key_of(x[r][q]));
       }
     }
-  }
+  };
+  constexpr int kShift = 31 - kRowSampleBits;
+  uint32_t s_cnt = 0;
+  sample([&](uint32_t key) {
+    atomicAdd(&shist[key >> kShift], 1u);
+    ++s_cnt;
+  });
   uint32_t s_n;
   row_scan(s_cnt, s_w, s_n);
   // sample ranks bracketing the k-th largest key
@@ -347,13 +361,38 @@ __device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t ve
   }
   if (tid == 0) s_res[0] = s_res[1] = s_res[2] = 0u;
   row_select_bin(shist, kRowSampleBits, r_lo, s_w, s_res);
-  t_lo = s_res[0] << (31 - kRowSampleBits);
+  const uint32_t lo = s_res[0], in_lo = r_lo - s_res[1];         // bin and rank within it
+  uint32_t hi = 0, in_hi = 0;
   __syncthreads();
-  t_hi = kKeyInf;
   if (r_hi >= 1) {
     if (tid == 0) s_res[0] = s_res[1] = s_res[2] = 0u;
     row_select_bin(shist, kRowSampleBits, r_hi, s_w, s_res);
-    t_hi = (s_res[0] + 1u) << (31 - kRowSampleBits);
+    hi = s_res[0];
+    in_hi = r_hi - s_res[1];
+    __syncthreads();
+  }
+  t_lo = lo << kShift;
+  t_hi = r_hi >= 1 ? (hi + 1u) << kShift : kKeyInf;
+  if (!refine || whole) return;
+  constexpr int kFine = kShift - kRowRefineBits;
+  constexpr uint32_t kN = 1u << kRowRefineBits;
+  static_assert(2 * kN <= kRowCand, "both bins' finer histograms fit the candidate array");
+  for (uint32_t i = tid; i < 2 * kN; i += kRowBlock) shist[i] = 0u;
+  __syncthreads();
+  sample([&](uint32_t key) {
+    const uint32_t b = key >> kShift, f = (key >> kFine) & (kN - 1u);
+    if (b == lo) atomicAdd(&shist[f], 1u);
+    if (r_hi >= 1 && b == hi) atomicAdd(&shist[kN + f], 1u);
+  });
+  if (tid == 0) s_res[0] = s_res[1] = s_res[2] = 0u;
+  __syncthreads();
+  row_select_bin(shist, kRowRefineBits, in_lo, s_w, s_res);
+  t_lo |= s_res[0] << kFine;
+  __syncthreads();
+  if (r_hi >= 1) {
+    if (tid == 0) s_res[0] = s_res[1] = s_res[2] = 0u;
+    row_select_bin(shist + kN, kRowRefineBits, in_hi, s_w, s_res);
+    t_hi = (hi << kShift) + ((s_res[0] + 1u) << kFine);
     __syncthreads();
   }
 }
@@ -426,14 +465,24 @@ __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
   __shared__ uint32_t s_res[4];
   __shared__ double s_d[kRowWaves];
   __shared__ uint32_t s_chunk[2 * kRowChunks];
-  const RowDesc d = rc.rows[rc.Lb * rc.K + blockIdx.x];
+  const RowDesc d = rc.rows[blockIdx.x];
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
   const Row row{gptr(d.grad), ((uint64_t)d.grad >> 2) & 3u, d.n};
   const uint64_t vend = (uint64_t)d.n + row.shift;
 
-  // 1. bracket from the sample
+  // 1. bracket from the sample; that is all a split row needs here
   uint32_t t_lo, t_hi;
-  row_bracket(d, row, vend, cand, s_w, s_res, t_lo, t_hi);
+  row_bracket(d, row, vend, blockIdx.x < rc.Lb * rc.K, cand, s_w, s_res, t_lo, t_hi);
+  if (blockIdx.x < rc.Lb * rc.K) {
+    if (tid == 0) {
+      BigRowState st;
+      __builtin_memset(&st, 0, sizeof(st));
+      st.t_lo = t_lo;
+      st.t_hi = t_hi;
+      rc.bst[blockIdx.x] = st;
+    }
+    return;
+  }
 
   // 2. one read: keys >= t_hi counted, keys in [t_lo, t_hi) gathered, sum g^2
   if (tid == 0) s_res[3] = 0u;
@@ -581,8 +630,9 @@ __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
 
 // ---- split rows --------------------------------------------------------------------------
 // A row longer than the split threshold is read by one workgroup per part:
-//   k_big_bracket  one workgroup per row: the sampled bracket [t_lo, t_hi)
-//                  (as k_rows computes it);
+//   k_rows         its first workgroups, one per row: the sampled bracket
+//                  [t_lo, t_hi) (the short rows' selections of the same launch
+//                  fill the compute units the few brackets leave);
 //   k_big_gather   one workgroup per part, the one read of the row: sum of
 //                  g^2 and, per chunk, the keys >= t_hi counted and the
 //                  candidates (keys >= t_lo) staged in index order in the
@@ -596,13 +646,12 @@ __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
 //                  written here, by this workgroup alone, as k_rows does it;
 //   k_big_write    one workgroup per part: every chunk's kept entries, from its
 //                  candidates, at the positions from its prefix;
-//   k_big_finish   the kept energy of each row from its waves' sums, in order.
+//   k_rows_energy  the kept energy of each row from its waves' sums, in order,
+//                  then the device's.
 // No workgroup waits for another inside a launch, and the part kernels have
 // no barrier and no atomic but the rare overflow flag.
 constexpr int kPartWaves = (int)kRowPartWaves;
-// selection-interval keys a split row's select workgroup holds in LDS (one
-// workgroup per row: it can take most of a compute unit's 160 KiB)
-constexpr int kBigCand = 32768;
+constexpr int kBigCand = (int)kRowBigCand;
 static_assert(kBigCand >= kRowCand, "the whole-row path of the select kernel uses kRowCand keys of the array");
 constexpr int kPartBlock = 64 * kPartWaves;
 constexpr int kWaveChunks = kRowPartChunks / kPartWaves;    // chunks of one wave, loaded at once
@@ -617,18 +666,24 @@ struct PartOf {
 
 __device__ inline PartOf part_of(const RowsCtx& rc, uint32_t g)
 {
+  // 64 prefixes per load and a ballot: the last q with pre[q] * K <= g (a binary
+  // search waits for memory at every step, ahead of the part's own loads)
   const uint64_t* pre = rc.table + 2ull * rc.L + 1;
-  uint32_t lo = 0, hi = rc.Lb;     // pre[lo] * K <= g < pre[hi] * K
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) / 2;
-    if (pre[mid] * rc.K <= g) lo = mid;
-    else hi = mid;
+  const uint32_t l = lane_id();
+  uint32_t q = 0;
+  for (uint32_t i0 = 0; i0 < rc.Lb; i0 += 64) {
+    const uint32_t i = i0 + l;
+    const uint32_t n = (uint32_t)__builtin_popcountll(ballot(i < rc.Lb && pre[i < rc.Lb ? i : 0] * rc.K <= g));
+    q += n;
+    if (n < 64) break;
   }
-  const uint32_t np = (uint32_t)(pre[lo + 1] - pre[lo]);
-  const uint32_t rel = g - (uint32_t)(pre[lo] * rc.K);
+  q = (uint32_t)__builtin_amdgcn_readfirstlane(q) - 1u;        // pre[0] = 0: at least one
+  const uint64_t p0 = pre[q], p1 = pre[q + 1];
+  const uint32_t np = (uint32_t)(p1 - p0);
+  const uint32_t rel = g - (uint32_t)(p0 * rc.K);
   const uint32_t j = rel / np;
   PartOf r;
-  r.b = lo * rc.K + j;
+  r.b = q * rc.K + j;
   r.p = rel - j * np;
   r.g0 = g - r.p;
   r.np = np;
@@ -663,55 +718,19 @@ __device__ inline double wave_sum_list(const double* a, uint32_t n)
   return wave_sum_f64(v);
 }
 
-__global__ __launch_bounds__(kRowBlock) void k_big_bracket(RowsCtx rc)
-{
-  __shared__ uint32_t shist[1 << kRowSampleBits];
-  __shared__ uint32_t s_w[kRowWaves];
-  __shared__ uint32_t s_res[4];
-  const RowDesc d = rc.rows[blockIdx.x];
-  const Row row{gptr(d.grad), ((uint64_t)d.grad >> 2) & 3u, d.n};
-  uint32_t t_lo, t_hi;
-  row_bracket(d, row, (uint64_t)d.n + row.shift, shist, s_w, s_res, t_lo, t_hi);
-  if (threadIdx.x == 0) {
-    BigRowState st;
-    __builtin_memset(&st, 0, sizeof(st));
-    st.t_lo = t_lo;
-    st.t_hi = t_hi;
-    rc.bst[blockIdx.x] = st;
-  }
-}
-
-// Gather-pass counts of one chunk in one wave (x holds its kRowR rounds: lane
-// l has elements v0 + r * 256 + 4 l .. + 3 of round r): keys >= t_hi and
-// candidates (keys >= t_lo); e_all accumulates g^2. kFull: every element is in
-// the row.
+// Gather pass over one chunk in one wave (x holds its kRowR rounds: lane l has
+// elements v0 + r * 256 + 4 l .. + 3 of round r): counts keys >= t_hi and
+// candidates (keys >= t_lo) and stages the latter at position at .. of the wave's
+// region in index order (round, lane, component): the first kGatherStage in
+// LDS, written out together at the end, the rest at cand, at most up to position
+// cap; e_all accumulates g^2. kFull: every element is in the row.
+constexpr uint32_t kGatherStage = 256;
 template <bool kFull>
-__device__ inline void gather_count(const f4 (&x)[kRowR], uint64_t v0, uint64_t vend, const Row& row, uint32_t t_lo,
-                                    uint32_t t_hi, uint32_t& nsure, uint32_t& ncand, uint32_t& nband, double& e_all)
+__device__ inline void gather_chunk(const f4 (&x)[kRowR], uint64_t v0, uint64_t vend, const Row& row, uint32_t t_lo,
+                                    uint32_t t_hi, uint32_t at, uint64_t* stage, GLOBAL uint64_t* cand, uint32_t cap,
+                                    uint32_t& nsure, uint32_t& ncand, double& e_all)
 {
-  nsure = ncand = nband = 0;
-#pragma unroll
-  for (int r = 0; r < kRowR; ++r) {
-    const uint64_t v = v0 + r * 256u;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bool valid = kFull || (v < vend && in_row(row, v + q));
-      const uint32_t key = key_of(x[r][q]);
-      nsure += (uint32_t)__builtin_popcountll(ballot(valid && key >= t_hi));
-      ncand += (uint32_t)__builtin_popcountll(ballot(valid && key >= t_lo));
-      nband += (uint32_t)__builtin_popcountll(ballot(valid && key >= t_lo && key < t_hi));
-      if (kFull) e_all = __builtin_fma((double)x[r][q], (double)x[r][q], e_all);
-      else if (valid) e_all = __builtin_fma((double)x[r][q], (double)x[r][q], e_all);
-    }
-  }
-}
-
-// Stages one chunk's candidates at cand[at ..] (index order: round, lane,
-// component), at most up to position cap.
-template <bool kFull>
-__device__ inline void gather_write(const f4 (&x)[kRowR], uint64_t v0, uint64_t vend, const Row& row, uint32_t t_lo,
-                                    uint32_t at, GLOBAL uint64_t* cand, uint32_t cap)
-{
+  nsure = ncand = 0;
 #pragma unroll
   for (int r = 0; r < kRowR; ++r) {
     const uint64_t v = v0 + r * 256u;
@@ -720,27 +739,38 @@ __device__ inline void gather_write(const f4 (&x)[kRowR], uint64_t v0, uint64_t 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const bool valid = kFull || (v < vend && in_row(row, v + q));
-      f[q] = valid && key_of(x[r][q]) >= t_lo;
+      const uint32_t key = key_of(x[r][q]);
+      f[q] = valid && key >= t_lo;
       bc[q] = ballot(f[q]);
+      if (kFull) e_all = __builtin_fma((double)x[r][q], (double)x[r][q], e_all);
+      else if (valid) e_all = __builtin_fma((double)x[r][q], (double)x[r][q], e_all);
     }
-    if ((bc[0] | bc[1] | bc[2] | bc[3]) == 0ull) continue;
-    uint32_t cp = at + mbcnt(bc[0]) + mbcnt(bc[1]) + mbcnt(bc[2]) + mbcnt(bc[3]);
+    if (bc[0] | bc[1] | bc[2] | bc[3]) {
+      uint32_t cp = at + ncand + mbcnt(bc[0]) + mbcnt(bc[1]) + mbcnt(bc[2]) + mbcnt(bc[3]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (f[q]) {
-        if (cp < cap) cand[cp] = (uint64_t)(uint32_t)(v + q - row.shift) | ((uint64_t)__float_as_uint(x[r][q]) << 32);
-        ++cp;
+      for (int q = 0; q < 4; ++q) {
+        nsure += (uint32_t)__builtin_popcountll(ballot(f[q] && key_of(x[r][q]) >= t_hi));
+        if (f[q]) {
+          const uint64_t e = (uint64_t)(uint32_t)(v + q - row.shift) | ((uint64_t)__float_as_uint(x[r][q]) << 32);
+          if (cp < kGatherStage) stage[cp] = e;
+          else if (cp < cap) cand[cp] = e;
+          ++cp;
+        }
       }
+      ncand += (uint32_t)(__builtin_popcountll(bc[0]) + __builtin_popcountll(bc[1]) + __builtin_popcountll(bc[2]) +
+                          __builtin_popcountll(bc[3]));
     }
-    at += (uint32_t)(__builtin_popcountll(bc[0]) + __builtin_popcountll(bc[1]) + __builtin_popcountll(bc[2]) +
-                     __builtin_popcountll(bc[3]));
+    __builtin_amdgcn_sched_barrier(0);    // keep rounds apart: bounds the live ballot masks
   }
 }
 
 // Each wave loads its kWaveChunks consecutive chunks at once, counts them and
-// stages their candidates in its region.
-__global__ __launch_bounds__(kPartBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_big_gather(RowsCtx rc)
+// stages their candidates in its region: by way of LDS, so that they leave as a
+// contiguous run (lane by lane, the stores of 1% of the elements cost a quarter
+// of the pass: 8 x 9.9 M, 76 -> 70 us).
+__global__ __launch_bounds__(kPartBlock) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_big_gather(RowsCtx rc)
 {
+  __shared__ uint64_t s_c[kPartWaves][kGatherStage];
   const PartOf po = part_of(rc, blockIdx.x);
   const RowDesc d = rc.rows[po.b];
   GLOBAL BigRowState* st = gptr(rc.bst) + po.b;
@@ -779,19 +809,18 @@ __global__ __launch_bounds__(kPartBlock) __attribute__((amdgpu_waves_per_eu(4, 4
 #pragma unroll
   for (int c = 0; c < kWaveChunks; ++c) {
     const uint64_t vc = v0 + (uint64_t)c * kRowChunkLen;
-    uint32_t nsure, ncand, nband;
-    if (full) gather_count<true>(x[c], vc, vend, row, t_lo, t_hi, nsure, ncand, nband, e_all);
-    else gather_count<false>(x[c], vc, vend, row, t_lo, t_hi, nsure, ncand, nband, e_all);
-    if (ncand) {
-      if (full) gather_write<true>(x[c], vc, vend, row, t_lo, at, cand, wcap);
-      else gather_write<false>(x[c], vc, vend, row, t_lo, at, cand, wcap);
-    }
+    uint32_t nsure, ncand;
+    if (full) gather_chunk<true>(x[c], vc, vend, row, t_lo, t_hi, at, s_c[w], cand, wcap, nsure, ncand, e_all);
+    else gather_chunk<false>(x[c], vc, vend, row, t_lo, t_hi, at, s_c[w], cand, wcap, nsure, ncand, e_all);
     if (lane == 0) {
-      const u4 w4 = {nsure, nband, wbase + at, ncand};
+      const u4 w4 = {nsure, ncand - nsure, wbase + at, ncand};
       *reinterpret_cast<GLOBAL u4*>(rec + c * kChunkWords) = w4;
     }
     at += ncand;
   }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // other lanes' entries
+  const uint32_t staged = at < kGatherStage ? (at < wcap ? at : wcap) : (wcap < kGatherStage ? wcap : kGatherStage);
+  for (uint32_t e = lane; e < staged; e += 64) cand[e] = s_c[w][e];
   if (at > wcap && lane == 0) __hip_atomic_fetch_or(&st->ovf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const double e = wave_sum_f64(e_all);
   if (lane == 0) rc.part_e[(uint64_t)blockIdx.x * kPartWaves + w] = e;
@@ -967,30 +996,31 @@ __global__ __launch_bounds__(kPartBlock) void k_big_write(RowsCtx rc)
   if (lane == 0) rc.part_e[((uint64_t)rc.nparts + blockIdx.x) * kPartWaves + w] = e;
 }
 
-__global__ __launch_bounds__(64) void k_big_finish(RowsCtx rc)
+// Per device: the kept energies of its split rows (a wave per row), then the
+// energies of all its layers, short and long (each lane a strided subset in
+// layer order, then the lanes in a fixed tree).
+constexpr int kEnergyBlock = 1024;
+__global__ __launch_bounds__(kEnergyBlock) void k_rows_energy(RowsCtx rc, double* energies)
 {
-  const uint32_t b = blockIdx.x;
-  if (rc.bst[b].slow) return;
-  uint32_t g0, np;
-  row_parts(rc, b, g0, np);
-  const double ek = wave_sum_list(rc.part_e + ((uint64_t)rc.nparts + g0) * kPartWaves, np * kPartWaves);
-  if (threadIdx.x == 0) rc.row_e[2ull * rc.rows[b].eslot + 1] = ek;
-}
-
-// Per device: the energies of all its layers, short and long (each lane a
-// strided subset in layer order, then the lanes in a fixed tree).
-__global__ __launch_bounds__(64) void k_rows_energy(RowsCtx rc, double* energies)
-{
-  // lane i adds layers i, i + 64, ... in order, then the lanes in a fixed tree
-  const uint32_t j = blockIdx.x;
+  const uint32_t j = blockIdx.x, lane = lane_id();
+  for (uint32_t q = threadIdx.x >> 6; q < rc.Lb; q += kEnergyBlock / 64) {
+    const uint32_t b = q * rc.K + j;
+    if (rc.bst[b].slow) continue;               // the select kernel wrote the row and its energy
+    uint32_t g0, np;
+    row_parts(rc, b, g0, np);
+    const double ek = wave_sum_list(rc.part_e + ((uint64_t)rc.nparts + g0) * kPartWaves, np * kPartWaves);
+    if (lane == 0) rc.row_e[2ull * rc.rows[b].eslot + 1] = ek;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
   double ea = 0.0, ek = 0.0;
-  for (uint32_t l = threadIdx.x; l < rc.L; l += 64) {
+  for (uint32_t l = lane; l < rc.L; l += 64) {
     ea += rc.row_e[2ull * ((uint64_t)j * rc.L + l)];
     ek += rc.row_e[2ull * ((uint64_t)j * rc.L + l) + 1];
   }
   ea = wave_sum_f64(ea);
   ek = wave_sum_f64(ek);
-  if (threadIdx.x != 0) return;
+  if (lane != 0) return;
   energies[2 * j] = ea;
   energies[2 * j + 1] = ek;
 }
@@ -1020,31 +1050,27 @@ hipError_t launch_layers_decide(const DecideArgs& a, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_put_table(const uint64_t* src, uint64_t count, uint64_t* dst, hipStream_t s)
+hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* table, uint64_t count, double* energies,
+                       hipStream_t s)
 {
+  uint64_t* dst = const_cast<uint64_t*>(rc.table);
+  PutArgs a;
+  __builtin_memset(&a, 0, sizeof(a));
   for (uint64_t at = 0; at < count; at += kPutWords) {
-    PutArgs a;
     a.count = (uint32_t)(count - at < (uint64_t)kPutWords ? count - at : (uint64_t)kPutWords);
-    for (uint32_t i = 0; i < a.count; ++i) a.v[i] = src[at + i];
+    for (uint32_t i = 0; i < a.count; ++i) a.v[i] = table[at + i];
     a.dst = dst + at;
-    k_put<<<1, 256, 0, s>>>(a);
+    if (count > kPutWords) k_put<<<1, 256, 0, s>>>(a);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, double* energies, hipStream_t s)
-{
-  k_rows_prep<<<rc.K, 256, 0, s>>>(rc, rp);
+  if (count > kPutWords) a.count = 0;
+  k_rows_prep<<<rc.K, 256, 0, s>>>(rc, rp, a);
+  if (rc.Ls > 0) k_rows<<<rc.Ls * rc.K, kRowBlock, 0, s>>>(rc);
   if (rc.Lb > 0) {
-    const uint32_t nb = rc.Lb * rc.K;
-    k_big_bracket<<<nb, kRowBlock, 0, s>>>(rc);
     k_big_gather<<<rc.nparts, kPartBlock, 0, s>>>(rc);
-    k_big_select<<<nb, kRowBlock, 0, s>>>(rc);
+    k_big_select<<<rc.Lb * rc.K, kRowBlock, 0, s>>>(rc);
     k_big_write<<<rc.nparts, kPartBlock, 0, s>>>(rc);
-    k_big_finish<<<nb, 64, 0, s>>>(rc);
   }
-  if (rc.Ls > rc.Lb) k_rows<<<(rc.Ls - rc.Lb) * rc.K, kRowBlock, 0, s>>>(rc);
-  if (rc.Ls > 0 && energies) k_rows_energy<<<rc.K, 64, 0, s>>>(rc, energies);
+  if (rc.Ls > 0 && energies) k_rows_energy<<<rc.K, kEnergyBlock, 0, s>>>(rc, energies);
   return hipGetLastError();
 }
 
@@ -1061,9 +1087,10 @@ hipError_t launch_zero_words(uint32_t* p, uint32_t n, hipStream_t s)
   return hipGetLastError();
 }
 
+// After everything, where there are long layers.
 hipError_t launch_rows_energy(const RowsCtx& rc, double* energies, hipStream_t s)
 {
-  k_rows_energy<<<rc.K, 64, 0, s>>>(rc, energies);
+  k_rows_energy<<<rc.K, kEnergyBlock, 0, s>>>(rc, energies);
   return hipGetLastError();
 }
 

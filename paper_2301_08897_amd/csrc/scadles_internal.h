@@ -31,6 +31,7 @@ constexpr uint32_t kKeyMask = 0x7FFFFFFFu;
 constexpr uint64_t kSat31 = 0x7FFFFFFFull;
 constexpr int kFullWorkers = 1024;     // grid-stride workgroups of the exact path's histogram passes
 constexpr int kHotWorkers = 4096;      // grid-stride workgroups for hot tiles
+constexpr int kBesideWorkers = 256;    // both, beside another selection's main pass
 constexpr int kWaveCap = 512;          // main pass: candidates one wave chunk (4096 elements) can stage
 constexpr int kSlotWords = 1024;       // 32-bit words of one tile's slot region (4 KiB)
 
@@ -224,7 +225,7 @@ __device__ inline void momentum_step(float& p, float& v, float g, double nlr, do
 // selection once per layer.
 constexpr int kRowBlock = 1024;
 constexpr int kRowCand = 14336;        // keys of the threshold bin held in LDS
-constexpr int kPutWords = 240;         // table words per k_put launch (kernel-argument copy)
+constexpr int kPutWords = 200;         // table words per k_put launch (kernel-argument copy)
 
 struct RowDesc {
   const float* grad;     // the layer's first element
@@ -254,6 +255,10 @@ constexpr uint32_t kRowPartWaves = 4;       // waves of a part workgroup
 constexpr uint64_t kRowWaveLen = kRowPartLen / kRowPartWaves;   // elements of one wave in a part
 constexpr uint64_t kRowSplitMin = 65536;   // smallest row that may be split
 constexpr uint64_t kRowSplitMax = 1u << 24; // longest row that may be split
+// Selection-interval keys a split row's select workgroup holds in LDS (one
+// workgroup per row: it can take most of a compute unit's 160 KiB).
+constexpr uint32_t kRowBigCand = 32768;
+constexpr uint32_t kRowSampleEvery = 16;    // a row's sample: one in this many elements
 constexpr uint32_t kChunkWords = 4;         // words of a chunk's record
 
 // Per split row: its bracket, whether some wave's candidates overflowed their
@@ -290,7 +295,6 @@ struct RowsCtx {
   double* part_e;         // [2 x nparts x 4] E_all, then E_kept, partial sums per wave of each part
 };
 
-hipError_t launch_put_table(const uint64_t* src, uint64_t count, uint64_t* dst, hipStream_t s);
 
 // Decision of the per-layer fused step.
 struct DecideArgs {
@@ -306,8 +310,10 @@ struct DecideArgs {
   uint32_t k[kMaxK];        // entries kept per device
 };
 hipError_t launch_layers_decide(const DecideArgs& a, hipStream_t s);
-hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, double* energies, hipStream_t s);
-// energies = the short layers' energies (layer order) + add (the long layers', or null)
+// Table (copied to rc.table), preparation and selection of the short layers' rows;
+// energies (null: launch_rows_energy follows later) = all layers' sums per device.
+hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* table, uint64_t count, double* energies,
+                       hipStream_t s);
 hipError_t launch_rows_energy(const RowsCtx& rc, double* energies, hipStream_t s);
 hipError_t launch_zero_words(uint32_t* p, uint32_t n, hipStream_t s);
 

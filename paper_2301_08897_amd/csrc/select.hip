@@ -1201,70 +1201,85 @@ __device__ inline void write_staged(const Ctx& c, uint32_t j, uint32_t s, uint32
   }
 }
 
-// A hot tile, read from the gradient again by a workgroup, every wave its
-// kHotWindows windows of 64 elements, one per lane, all of them in registers: the
-// wave counts its keys, the counts before it place it, and the kept entries of
-// a window leave as one contiguous run.
-constexpr int kWriteBlock = 512;
-constexpr int kWriteWaves = kWriteBlock / 64;
-constexpr int kHotWindows = kTile / kWriteBlock;
+// A hot tile, read from the gradient again by a workgroup of kWB threads, every
+// wave kHotWindows windows of 64 elements at once, one per lane, all of them in
+// registers: the wave counts its keys, the counts before it place it, and the
+// kept entries of a window leave as one contiguous run.
+constexpr int kHotWindows = 32;
 
+template <int kWB>
 __device__ inline void write_hot(const Ctx& c, const DevDesc& d, uint32_t s, uint32_t* s_n, Out& o)
 {
+  constexpr int kW = kWB / 64;
   const uint32_t l = lane_id(), w = wave_id();
-  const uint64_t vbase = (uint64_t)s * kTile, v0 = vbase + w * (kHotWindows * 64);
+  const uint64_t vbase = (uint64_t)s * kTile;
   const GLOBAL uint32_t* g = reinterpret_cast<const GLOBAL uint32_t*>(gptr(d.grad));
-  uint32_t x[kHotWindows];
-  if (vbase >= d.shift && vbase + kTile <= d.shift + c.n) {
-    const GLOBAL uint32_t* gw = g + (v0 - d.shift);
+  const uint32_t thr1 = o.thr + 1u;       // rank keys: pads are never above or equal
+  const bool full = vbase >= d.shift && vbase + kTile <= d.shift + c.n;
+#pragma unroll 1
+  for (uint32_t p = 0; p < (uint32_t)kTile; p += kWB * kHotWindows) {
+    const uint64_t v0 = vbase + p + w * (kHotWindows * 64);
+    uint32_t x[kHotWindows];
+    if (full) {
+      const GLOBAL uint32_t* gw = g + (v0 - d.shift);
 #pragma unroll
-    for (int m = 0; m < kHotWindows; ++m) x[m] = __builtin_nontemporal_load(gw + m * 64 + l);
-  } else {
-    // the (at most two) edge tiles of a device hold positions outside the gradient
+      for (int m = 0; m < kHotWindows; ++m) x[m] = __builtin_nontemporal_load(gw + m * 64 + l);
+    } else {
+      // the (at most two) edge tiles of a device hold positions outside the gradient
+#pragma unroll
+      for (int m = 0; m < kHotWindows; ++m) {
+        const uint64_t v = v0 + m * 64 + l, end = d.shift + c.n;
+        const uint64_t at = v < d.shift ? 0 : (v < end ? v - d.shift : c.n - 1);
+        const uint32_t y = g[at];
+        x[m] = v >= d.shift && v < end ? y : kPadBits;
+      }
+    }
+    uint32_t n = 0;                         // gt | eq << 16: at most 2048 each
 #pragma unroll
     for (int m = 0; m < kHotWindows; ++m) {
-      const uint64_t v = v0 + m * 64 + l, end = d.shift + c.n;
-      const uint64_t at = v < d.shift ? 0 : (v < end ? v - d.shift : c.n - 1);
-      const uint32_t y = g[at];
-      x[m] = v >= d.shift && v < end ? y : kPadBits;
+      const uint32_t key1 = rank_key(__uint_as_float(x[m]));
+      n += (uint32_t)__builtin_popcountll(ballot(key1 > thr1));
+      n += (uint32_t)__builtin_popcountll(ballot(key1 == thr1)) << 16;
+      __builtin_amdgcn_sched_barrier(0);    // keep windows apart: bounds the live ballot masks
     }
-  }
-  const uint32_t thr1 = o.thr + 1u;       // rank keys: pads are never above or equal
-  uint32_t n = 0;                         // gt | eq << 16: at most 2048 each
+    __syncthreads();                        // the counts before have been read
+    if (l == 0) s_n[w] = n;
+    __syncthreads();
+    // the counts of the waves before this one, and of all
+    uint32_t bg0 = 0, be0 = 0, ag = 0, ae = 0;
+    for (uint32_t i = 0; i < (uint32_t)kW; ++i) {
+      const uint32_t v = s_n[i];
+      if (i == w) {
+        bg0 = ag;
+        be0 = ae;
+      }
+      ag += v & 0xFFFFu;
+      ae += v >> 16;
+    }
+    const uint32_t next_g = o.run_g + ag, next_e = o.run_e + ae;
+    o.run_g += bg0;
+    o.run_e += be0;
+    // The one range start among the wave's positions, if any: its marker is the
+    // kept entries before that element (every element of the tile passes by).
+    static_assert(kHotWindows * 64 <= kARange, "a wave's positions hold one range start at most");
+    const uint64_t first = v0 > d.shift ? v0 - d.shift : 0;
+    const uint64_t start = (first + kARange - 1) / kARange * kARange;
+    const uint32_t mark = o.lb && start < c.n ? (uint32_t)(start + d.shift - v0) : 0xFFFFFFFFu;
+    const uint32_t i0 = (uint32_t)(v0 - d.shift);
 #pragma unroll
-  for (int m = 0; m < kHotWindows; ++m) {
-    const uint32_t key1 = rank_key(__uint_as_float(x[m]));
-    n += (uint32_t)__builtin_popcountll(ballot(key1 > thr1));
-    n += (uint32_t)__builtin_popcountll(ballot(key1 == thr1)) << 16;
-    __builtin_amdgcn_sched_barrier(0);    // keep windows apart: bounds the live ballot masks
-  }
-  __syncthreads();                        // the tile before has been read
-  if (l == 0) s_n[w] = n;
-  __syncthreads();
-  for (uint32_t i = 0; i < w; ++i) {
-    o.run_g += s_n[i] & 0xFFFFu;
-    o.run_e += s_n[i] >> 16;
-  }
-  // The one range start among the wave's positions, if any: its marker is the
-  // kept entries before that element (every element of the tile passes by).
-  static_assert(kHotWindows * 64 <= kARange, "a wave's positions hold one range start at most");
-  const uint64_t first = v0 > d.shift ? v0 - d.shift : 0;
-  const uint64_t start = (first + kARange - 1) / kARange * kARange;
-  const uint32_t mark = o.lb && start < c.n ? (uint32_t)(start + d.shift - v0) : 0xFFFFFFFFu;
-  const uint32_t i0 = (uint32_t)(v0 - d.shift);
-#pragma unroll
-  for (int m = 0; m < kHotWindows; ++m) {
-    asm volatile("" : "+v"(x[m]));        // the masks are made again, not kept from the count: 128 registers
-    const uint32_t key1 = rank_key(__uint_as_float(x[m]));
-    const bool fg = key1 > thr1, fe = key1 == thr1;
-    const uint64_t bg = ballot(fg), be = ballot(fe);
-    const uint32_t gt_b = o.run_g + mbcnt(bg), eq_b = o.run_e + mbcnt(be);
-    if (mark == (uint32_t)m * 64 + l) o.lb[start / kARange] = gt_b + (eq_b < o.need ? eq_b : o.need);
-    const uint32_t idx = i0 + m * 64 + l;
-    if (fg || (fe && eq_b < o.need)) put_entry(o, gt_b, eq_b, idx, __uint_as_float(x[m]));
-    o.run_g += (uint32_t)__builtin_popcountll(bg);
-    o.run_e += (uint32_t)__builtin_popcountll(be);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int m = 0; m < kHotWindows; ++m) {
+      const uint32_t key1 = rank_key(__uint_as_float(x[m]));
+      const bool fg = key1 > thr1, fe = key1 == thr1;
+      const uint64_t bg = ballot(fg), be = ballot(fe);
+      const uint32_t gt_b = o.run_g + mbcnt(bg), eq_b = o.run_e + mbcnt(be);
+      if (mark == (uint32_t)m * 64 + l) o.lb[start / kARange] = gt_b + (eq_b < o.need ? eq_b : o.need);
+      if (fg || (fe && eq_b < o.need)) put_entry(o, gt_b, eq_b, i0 + m * 64 + l, __uint_as_float(x[m]));
+      o.run_g += (uint32_t)__builtin_popcountll(bg);
+      o.run_e += (uint32_t)__builtin_popcountll(be);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    o.run_g = next_g;
+    o.run_e = next_e;
   }
 }
 
@@ -1310,16 +1325,21 @@ __global__ __launch_bounds__(kBlock) void k_final(Ctx c)
 // Output pass: staged tiles, kWriteTiles per wave (their counts and offsets
 // loaded together), and hot tiles, one per workgroup, read from the gradient
 // again. The kept sum of squares of each tile goes to ekept.
+// Workgroups of 512 threads, of 256 beside another selection's main pass, whose
+// small workgroups rarely leave 8 waves free at once (per-layer step of 16 x
+// 143.7 M: 2680 us against 2754).
 constexpr uint32_t kWriteTiles = 2;
+constexpr int kWriteLarge = 512, kWriteSmall = 256;
 
-__global__ __launch_bounds__(kWriteBlock) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_write(
-    Ctx c, uint32_t workers, uint32_t per_dev)
+template <int kWB>
+__global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_write(Ctx c, uint32_t workers,
+                                                                                          uint32_t per_dev)
 {
   const uint32_t l = lane_id(), w = wave_id();
   if (blockIdx.x >= workers) {
     const uint32_t b = blockIdx.x - workers;
     const uint32_t jr = b / per_dev, j = c.j0 + jr;
-    const uint32_t s0 = ((b - jr * per_dev) * kWriteWaves + w) * kWriteTiles;
+    const uint32_t s0 = ((b - jr * per_dev) * (kWB / 64) + w) * kWriteTiles;
     if (s0 >= c.nslot) return;
     const uint64_t row = (uint64_t)j * c.nslot;
     const bool live = l < kWriteTiles && s0 + l < c.nslot;
@@ -1340,21 +1360,21 @@ __global__ __launch_bounds__(kWriteBlock) __attribute__((amdgpu_waves_per_eu(7, 
     }
     return;
   }
-  __shared__ double s_e[kWriteWaves];
-  __shared__ uint32_t s_n[kWriteWaves];
+  __shared__ double s_e[kWB / 64];
+  __shared__ uint32_t s_n[kWB / 64];
   for_hot_tiles<true, true>(c, blockIdx.x, workers, [&](uint32_t j, uint32_t s) {
     const uint64_t slot = (uint64_t)j * c.nslot + s;
     const uint64_t pre = c.tile_pre[slot];
     Out o = out_of(c, j);
     o.run_g = (uint32_t)pre;
     o.run_e = (uint32_t)(pre >> 32);
-    write_hot(c, c.desc[j], s, s_n, o);
+    write_hot<kWB>(c, c.desc[j], s, s_n, o);
     const double es = wave_sum_f64(o.e2);
     if (l == 0) s_e[w] = es;
     __syncthreads();
     if (threadIdx.x == 0) {
       double e = s_e[0];
-      for (int i = 1; i < kWriteWaves; ++i) e += s_e[i];
+      for (int i = 1; i < kWB / 64; ++i) e += s_e[i];
       c.ekept[slot] = e;
     }
   });
@@ -1406,8 +1426,13 @@ static void launch_post(const Ctx& c, const SelectPlan& p, hipStream_t s, int ha
     else k_offsets<kScanLarge><<<c.jn, kScanLarge, 0, s>>>(c);
     return;
   }
-  const uint32_t per_dev = p.any_fast ? (c.nslot + kWriteTiles * kWriteWaves - 1) / (kWriteTiles * kWriteWaves) : 0u;
-  k_write<<<per_dev * c.jn + p.hot_workers, kWriteBlock, 0, s>>>(c, p.hot_workers, per_dev);
+  auto write = [&](auto kernel, int block) {
+    const uint32_t tiles = kWriteTiles * block / 64;
+    const uint32_t per_dev = p.any_fast ? (c.nslot + tiles - 1) / tiles : 0u;
+    kernel<<<per_dev * c.jn + p.hot_workers, block, 0, s>>>(c, p.hot_workers, per_dev);
+  };
+  if (p.beside) write(k_write<kWriteSmall>, kWriteSmall);
+  else write(k_write<kWriteLarge>, kWriteLarge);
   k_final<<<c.jn, kBlock, 0, s>>>(c);
 }
 
