@@ -1048,9 +1048,11 @@ __global__ __launch_bounds__(kBlock) void k_count(Ctx c, uint32_t workers, uint3
   });
 }
 
+// A tile's counts, gt | eq << 16, as gt | eq << 32.
+__device__ inline uint64_t counts_of(uint32_t n) { return (uint64_t)(n & 0xFFFFu) | ((uint64_t)(n >> 16) << 32); }
+
 // One workgroup per device: the exclusive prefix of its tiles' counts (gt | eq <<
-// 16) as gt | eq << 32, and the device's keys above the threshold. 1024
-// threads when it runs alone; 256 when it runs beside another selection's main
+// 16) as gt | eq << 32. 1024 threads when it runs alone; 256 when it runs beside another selection's main
 // pass, whose stream of small workgroups rarely leaves 16 waves of a compute
 // unit free at once.
 constexpr int kScanLarge = 1024, kScanSmall = 256;
@@ -1079,7 +1081,7 @@ __global__ __launch_bounds__(NT) void k_offsets(Ctx c)
     for (int i = 0; i < kPer; ++i) {
       const uint32_t x = h[tid * kPer + i];
       own[i] = sum;
-      sum += (uint64_t)(x & 0xFFFFu) | ((uint64_t)(x >> 16) << 32);
+      sum += counts_of(x);
     }
     const uint64_t incl = wave_incl_scan_u64(sum);
     if (lane_id() == 63) s_w[w] = incl;
@@ -1097,7 +1099,6 @@ __global__ __launch_bounds__(NT) void k_offsets(Ctx c)
     }
     __syncthreads();
   }
-  if (tid == 0) c.st[j].c_gt = (uint32_t)base;
 }
 
 // ---- 5. ordered output -----------------------------------------------------------------------
@@ -1202,15 +1203,13 @@ __device__ inline void write_staged(const Ctx& c, uint32_t j, uint32_t s, uint32
 }
 
 // A hot tile, read from the gradient again by a workgroup of kWB threads, every
-// wave kHotWindows windows of 64 elements at once, one per lane, all of them in
+// wave up to 32 windows of 64 elements at once, one per lane, all of them in
 // registers: the wave counts its keys, the counts before it place it, and the
 // kept entries of a window leave as one contiguous run.
-constexpr int kHotWindows = 32;
-
 template <int kWB>
 __device__ inline void write_hot(const Ctx& c, const DevDesc& d, uint32_t s, uint32_t* s_n, Out& o)
 {
-  constexpr int kW = kWB / 64;
+  constexpr int kW = kWB / 64, kHotWindows = kTile / kWB < 32 ? kTile / kWB : 32;
   const uint32_t l = lane_id(), w = wave_id();
   const uint64_t vbase = (uint64_t)s * kTile;
   const GLOBAL uint32_t* g = reinterpret_cast<const GLOBAL uint32_t*>(gptr(d.grad));
@@ -1295,19 +1294,26 @@ __global__ __launch_bounds__(kBlock) void k_final(Ctx c)
   DevState& s = c.st[j];
   const double* ea = c.epart + (uint64_t)j * c.nslot;
   const double* ek = c.ekept + (uint64_t)j * c.nslot;
+  const uint32_t* cnt = c.tile_cnt + (uint64_t)j * c.nslot;
   double all = 0.0, kept = 0.0;
+  uint64_t gt = 0;
 #pragma unroll 4
   for (uint32_t b = threadIdx.x; b < c.nslot; b += kBlock) {
     all += ea[b];
     kept += ek[b];
+    gt += cnt[b] & 0xFFFFu;
   }
-  const double e_all = block_sum_f64(all, s_e);
+  __shared__ uint64_t s_gt[kWaves];
+  gt = wave_sum_u64(gt);
+  if (lane_id() == 0) s_gt[threadIdx.x >> 6] = gt;
+  const double e_all = block_sum_f64(all, s_e);      // (its barrier covers s_gt)
   const double e_kept = block_sum_f64(kept, s_e);
   if (threadIdx.x != 0) return;
   uint32_t thr, need;
   if (!threshold_of(s, thr, need)) s.err |= kErrNoThreshold;
   s.thr = thr;
   s.need = need;
+  s.c_gt = (s_gt[0] + s_gt[1]) + (s_gt[2] + s_gt[3]);
   if (s.c_gt + s.need != c.desc[j].k || (c.inject_count_error && j == 0)) s.err |= kErrCount;
   if (c.err_acc && (s.err & kErrFatal)) atomicOr(c.err_acc + j, s.err & kErrFatal);
   s.e_all = e_all;
@@ -1322,30 +1328,58 @@ __global__ __launch_bounds__(kBlock) void k_final(Ctx c)
   if (c.compressed_out) c.compressed_out[j] = (uint8_t)s.sparse;
 }
 
-// Output pass: staged tiles, kWriteTiles per wave (their counts and offsets
-// loaded together), and hot tiles, one per workgroup, read from the gradient
-// again. The kept sum of squares of each tile goes to ekept.
-// Workgroups of 512 threads, of 256 beside another selection's main pass, whose
-// small workgroups rarely leave 8 waves free at once (per-layer step of 16 x
-// 143.7 M: 2680 us against 2754).
-constexpr uint32_t kWriteTiles = 2;
-constexpr int kWriteLarge = 512, kWriteSmall = 256;
+// Kept-above | equal << 32 counts of the device's tiles before tile s, by a
+// workgroup of NT threads (s_p: one word per wave).
+template <int NT>
+__device__ inline uint64_t tiles_before(const Ctx& c, uint32_t j, uint32_t s, uint64_t* s_p)
+{
+  const uint32_t* cnt = c.tile_cnt + (uint64_t)j * c.nslot;
+  uint64_t sum = 0;
+  for (uint32_t t = threadIdx.x; t < s; t += NT) sum += counts_of(cnt[t]);
+  sum = wave_sum_u64(sum);
+  __syncthreads();
+  if (lane_id() == 0) s_p[wave_id()] = sum;
+  __syncthreads();
+  uint64_t all = s_p[0];
+  for (int i = 1; i < NT / 64; ++i) all += s_p[i];
+  return all;
+}
 
-template <int kWB>
+// Output pass: staged tiles (kStaged), kWriteTiles per wave, and hot tiles (kHot),
+// one per workgroup, read from the gradient again. The kept sum of squares of
+// each tile goes to ekept. kOwnOffsets: the workgroup sums the counts of the tiles
+// before its own instead of reading a launch's offsets. (Launches of their own
+// for staged and hot tiles: 16 x 60.2 M 50 us against 58 in one, 16 x 25.6 M at
+// ratio 0.1 163 against 155, one of 143.7 M 19 against 15.)
+constexpr uint32_t kWriteTiles = 2;
+
+template <int kWB, bool kOwnOffsets>
 __global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_write(Ctx c, uint32_t workers,
                                                                                           uint32_t per_dev)
 {
+  constexpr int kW = kWB / 64;
+  __shared__ uint64_t s_p[kW];
   const uint32_t l = lane_id(), w = wave_id();
   if (blockIdx.x >= workers) {
     const uint32_t b = blockIdx.x - workers;
     const uint32_t jr = b / per_dev, j = c.j0 + jr;
-    const uint32_t s0 = ((b - jr * per_dev) * (kWB / 64) + w) * kWriteTiles;
-    if (s0 >= c.nslot) return;
+    const uint32_t tb = (b - jr * per_dev) * (kW * kWriteTiles), s0 = tb + w * kWriteTiles;
     const uint64_t row = (uint64_t)j * c.nslot;
     const bool live = l < kWriteTiles && s0 + l < c.nslot;
     const uint32_t va = live ? c.slot_cnt[row + s0 + l] : 0x8000u;
-    const uint64_t pre = c.tile_pre[row + s0 + (live ? l : 0u)];
-    if (c.st[j].fallback || ballot(!(va & 0x8000u)) == 0ull) return;
+    uint64_t pre;
+    if (kOwnOffsets) {
+      if (c.st[j].fallback) return;
+      static_assert(kW * kWriteTiles <= 64, "a wave scans its workgroup's tiles");
+      const uint32_t n = l < kW * kWriteTiles && tb + l < c.nslot ? c.tile_cnt[row + tb + l] : 0u;
+      const uint64_t base = tiles_before<kWB>(c, j, tb, s_p);
+      const uint64_t ex = base + wave_incl_scan_u64(counts_of(n)) - counts_of(n);
+      pre = __shfl(ex, w * kWriteTiles + (l < kWriteTiles ? l : 0u), 64);
+    } else {
+      pre = c.tile_pre[live ? row + s0 + l : row];
+      if (c.st[j].fallback) return;
+    }
+    if (ballot(!(va & 0x8000u)) == 0ull) return;
     Out o = out_of(c, j);
     const uint32_t shift = c.desc[j].shift;
     for (uint32_t i = 0; i < kWriteTiles; ++i) {
@@ -1360,11 +1394,11 @@ __global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(7, 8))) voi
     }
     return;
   }
-  __shared__ double s_e[kWB / 64];
-  __shared__ uint32_t s_n[kWB / 64];
+  __shared__ double s_e[kW];
+  __shared__ uint32_t s_n[kW];
   for_hot_tiles<true, true>(c, blockIdx.x, workers, [&](uint32_t j, uint32_t s) {
     const uint64_t slot = (uint64_t)j * c.nslot + s;
-    const uint64_t pre = c.tile_pre[slot];
+    const uint64_t pre = kOwnOffsets ? tiles_before<kWB>(c, j, s, s_p) : c.tile_pre[slot];
     Out o = out_of(c, j);
     o.run_g = (uint32_t)pre;
     o.run_e = (uint32_t)(pre >> 32);
@@ -1374,7 +1408,7 @@ __global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(7, 8))) voi
     __syncthreads();
     if (threadIdx.x == 0) {
       double e = s_e[0];
-      for (int i = 1; i < kWB / 64; ++i) e += s_e[i];
+      for (int i = 1; i < kW; ++i) e += s_e[i];
       c.ekept[slot] = e;
     }
   });
@@ -1409,6 +1443,11 @@ static void launch_threshold(const Ctx& c, const SelectPlan& p, hipStream_t s)
   k_count<kBT><<<walk * c.jn + p.hot_workers, kBlock, 0, s>>>(c, p.hot_workers, walk);
 }
 
+// Whether the output sums the counts of the tiles before its own itself: for up
+// to 1024 tiles (16.7 M elements) that is two loads per thread, less than a
+// launch (k_offsets, 4.8 us).
+static bool own_offsets(const Ctx& c, const SelectPlan& p) { return c.nslot <= 1024 && !p.beside; }
+
 // Everything after the main pass for devices [c.j0, c.j0 + c.jn), on stream s,
 // in two halves: 0, the threshold (path decision, radix passes, tile counts and
 // offsets), latency-bound and light on memory; 1, the output (ordered
@@ -1422,6 +1461,7 @@ static void launch_post(const Ctx& c, const SelectPlan& p, hipStream_t s, int ha
       case 8: launch_threshold<8>(c, p, s); break;
       default: launch_threshold<4>(c, p, s); break;
     }
+    if (own_offsets(c, p)) return;
     if (p.beside) k_offsets<kScanSmall><<<c.jn, kScanSmall, 0, s>>>(c);
     else k_offsets<kScanLarge><<<c.jn, kScanLarge, 0, s>>>(c);
     return;
@@ -1431,8 +1471,18 @@ static void launch_post(const Ctx& c, const SelectPlan& p, hipStream_t s, int ha
     const uint32_t per_dev = p.any_fast ? (c.nslot + tiles - 1) / tiles : 0u;
     kernel<<<per_dev * c.jn + p.hot_workers, block, 0, s>>>(c, p.hot_workers, per_dev);
   };
-  if (p.beside) write(k_write<kWriteSmall>, kWriteSmall);
-  else write(k_write<kWriteLarge>, kWriteLarge);
+  // A hot tile's time is its workgroup's: 16 waves where a few tiles are all
+  // there is (4 x 61,706: 11.5 us against 17), 8 else (8 x 11.2 M: 34 against 40),
+  // 4 beside a main pass, which rarely leaves 8 free at once (per-layer step of 16
+  // x 143.7 M: 2680 against 2754).
+  if (!own_offsets(c, p)) {
+    if (p.beside) write(k_write<256, false>, 256);
+    else write(k_write<512, false>, 512);
+  } else if ((uint64_t)c.jn * c.nslot <= 512) {
+    write(k_write<1024, true>, 1024);
+  } else {
+    write(k_write<512, true>, 512);
+  }
   k_final<<<c.jn, kBlock, 0, s>>>(c);
 }
 
