@@ -593,7 +593,7 @@ static bool row_layer(uint64_t n, const double* ratios, uint32_t K)
   const int64_t most = g_row_max.load();
   if (most != kRowMaxAuto) return n <= (uint64_t)most;
   if (n <= (1u << 21)) return true;
-  if (n > (1u << 22) || row_cand_list(n, ratios, K) == 0) return false;
+  if (n > (1u << 22) || n <= (uint64_t)g_row_split.load() || row_cand_list(n, ratios, K) == 0) return false;
   uint64_t kmax = 0;
   for (uint32_t j = 0; j < K; ++j) kmax = std::max<uint64_t>(kmax, k_rule(n, ratios[j]));
   const double sample_k = (double)kmax / kRowSampleEvery;
