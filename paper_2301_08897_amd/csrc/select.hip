@@ -1205,11 +1205,17 @@ __device__ inline void write_staged(const Ctx& c, uint32_t j, uint32_t s, uint32
 // A hot tile, read from the gradient again by a workgroup of kWB threads, every
 // wave up to 32 windows of 64 elements at once, one per lane, all of them in
 // registers: the wave counts its keys, the counts before it place it, and the
-// kept entries of a window leave as one contiguous run.
+// kept entries of a window leave as one contiguous run. The kept squares of
+// every kHotSum windows (lanes in window order, then a fixed tree) go to s_e: the
+// tile's energy is their sum in order, the same for every kWB.
+constexpr int kHotSum = 16;
+constexpr int kHotSums = kTile / (kHotSum * 64);
+
 template <int kWB>
-__device__ inline void write_hot(const Ctx& c, const DevDesc& d, uint32_t s, uint32_t* s_n, Out& o)
+__device__ inline void write_hot(const Ctx& c, const DevDesc& d, uint32_t s, uint32_t* s_n, double* s_e, Out& o)
 {
   constexpr int kW = kWB / 64, kHotWindows = kTile / kWB < 32 ? kTile / kWB : 32;
+  static_assert(kHotWindows % kHotSum == 0, "a wave's windows are whole partial sums");
   const uint32_t l = lane_id(), w = wave_id();
   const uint64_t vbase = (uint64_t)s * kTile;
   const GLOBAL uint32_t* g = reinterpret_cast<const GLOBAL uint32_t*>(gptr(d.grad));
@@ -1275,6 +1281,11 @@ __device__ inline void write_hot(const Ctx& c, const DevDesc& d, uint32_t s, uin
       if (fg || (fe && eq_b < o.need)) put_entry(o, gt_b, eq_b, i0 + m * 64 + l, __uint_as_float(x[m]));
       o.run_g += (uint32_t)__builtin_popcountll(bg);
       o.run_e += (uint32_t)__builtin_popcountll(be);
+      if (m % kHotSum == kHotSum - 1) {
+        const double es = wave_sum_f64(o.e2);
+        if (l == 0) s_e[(p / 64 + w * kHotWindows + m) / kHotSum] = es;
+        o.e2 = 0.0;
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     o.run_g = next_g;
@@ -1394,7 +1405,7 @@ __global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(7, 8))) voi
     }
     return;
   }
-  __shared__ double s_e[kW];
+  __shared__ double s_e[kHotSums];
   __shared__ uint32_t s_n[kW];
   for_hot_tiles<true, true>(c, blockIdx.x, workers, [&](uint32_t j, uint32_t s) {
     const uint64_t slot = (uint64_t)j * c.nslot + s;
@@ -1402,13 +1413,11 @@ __global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(7, 8))) voi
     Out o = out_of(c, j);
     o.run_g = (uint32_t)pre;
     o.run_e = (uint32_t)(pre >> 32);
-    write_hot<kWB>(c, c.desc[j], s, s_n, o);
-    const double es = wave_sum_f64(o.e2);
-    if (l == 0) s_e[w] = es;
+    write_hot<kWB>(c, c.desc[j], s, s_n, s_e, o);
     __syncthreads();
     if (threadIdx.x == 0) {
       double e = s_e[0];
-      for (int i = 1; i < kW; ++i) e += s_e[i];
+      for (int i = 1; i < kHotSums; ++i) e += s_e[i];
       c.ekept[slot] = e;
     }
   });
