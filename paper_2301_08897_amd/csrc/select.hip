@@ -1203,19 +1203,20 @@ __device__ inline void write_staged(const Ctx& c, uint32_t j, uint32_t s, uint32
 }
 
 // A hot tile, read from the gradient again by a workgroup of kWB threads, every
-// wave up to 32 windows of 64 elements at once, one per lane, all of them in
+// wave kHotWindows windows of 64 elements at once, one per lane, all of them in
 // registers: the wave counts its keys, the counts before it place it, and the
-// kept entries of a window leave as one contiguous run. The kept squares of
-// every kHotSum windows (lanes in window order, then a fixed tree) go to s_e: the
-// tile's energy is their sum in order, the same for every kWB.
-constexpr int kHotSum = 16;
-constexpr int kHotSums = kTile / (kHotSum * 64);
+// kept entries of a window leave as one contiguous run. 16 windows leave the
+// kernel 64 registers, 8 waves per SIMD (32 took 72, and the 256-thread kernel
+// spilled: see k_write). Their kept squares (lanes in window order, then a
+// fixed tree) go to s_e: the tile's energy is the sum of s_e in order, the same for
+// every kWB.
+constexpr int kHotWindows = 16;
+constexpr int kHotSums = kTile / (kHotWindows * 64);
 
 template <int kWB>
 __device__ inline void write_hot(const Ctx& c, const DevDesc& d, uint32_t s, uint32_t* s_n, double* s_e, Out& o)
 {
-  constexpr int kW = kWB / 64, kHotWindows = kTile / kWB < 32 ? kTile / kWB : 32;
-  static_assert(kHotWindows % kHotSum == 0, "a wave's windows are whole partial sums");
+  constexpr int kW = kWB / 64;
   const uint32_t l = lane_id(), w = wave_id();
   const uint64_t vbase = (uint64_t)s * kTile;
   const GLOBAL uint32_t* g = reinterpret_cast<const GLOBAL uint32_t*>(gptr(d.grad));
@@ -1239,7 +1240,7 @@ __device__ inline void write_hot(const Ctx& c, const DevDesc& d, uint32_t s, uin
         x[m] = v >= d.shift && v < end ? y : kPadBits;
       }
     }
-    uint32_t n = 0;                         // gt | eq << 16: at most 2048 each
+    uint32_t n = 0;                         // gt | eq << 16: at most 1024 each
 #pragma unroll
     for (int m = 0; m < kHotWindows; ++m) {
       const uint32_t key1 = rank_key(__uint_as_float(x[m]));
@@ -1281,13 +1282,11 @@ __device__ inline void write_hot(const Ctx& c, const DevDesc& d, uint32_t s, uin
       if (fg || (fe && eq_b < o.need)) put_entry(o, gt_b, eq_b, i0 + m * 64 + l, __uint_as_float(x[m]));
       o.run_g += (uint32_t)__builtin_popcountll(bg);
       o.run_e += (uint32_t)__builtin_popcountll(be);
-      if (m % kHotSum == kHotSum - 1) {
-        const double es = wave_sum_f64(o.e2);
-        if (l == 0) s_e[(p / 64 + w * kHotWindows + m) / kHotSum] = es;
-        o.e2 = 0.0;
-      }
       __builtin_amdgcn_sched_barrier(0);
     }
+    const double es = wave_sum_f64(o.e2);
+    if (l == 0) s_e[p / (kHotWindows * 64) + w] = es;
+    o.e2 = 0.0;
     o.run_g = next_g;
     o.run_e = next_e;
   }
@@ -1356,58 +1355,57 @@ __device__ inline uint64_t tiles_before(const Ctx& c, uint32_t j, uint32_t s, ui
   return all;
 }
 
-// Output pass: staged tiles (kStaged), kWriteTiles per wave, and hot tiles (kHot),
-// one per workgroup, read from the gradient again. The kept sum of squares of
+// Output pass over the staged tiles of device b / per_dev of the launch,
+// kWriteTiles per wave, by workgroup b of kWB threads. The kept sum of squares of
 // each tile goes to ekept. kOwnOffsets: the workgroup sums the counts of the tiles
-// before its own instead of reading a launch's offsets. (Launches of their own
-// for staged and hot tiles: 16 x 60.2 M 50 us against 58 in one, 16 x 25.6 M at
-// ratio 0.1 163 against 155, one of 143.7 M 19 against 15.)
+// before its own instead of reading a launch's offsets.
 constexpr uint32_t kWriteTiles = 2;
 
 template <int kWB, bool kOwnOffsets>
-__global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_write(Ctx c, uint32_t workers,
-                                                                                          uint32_t per_dev)
+__device__ inline void write_staged_tiles(const Ctx& c, uint32_t b, uint32_t per_dev, uint64_t* s_p)
 {
   constexpr int kW = kWB / 64;
-  __shared__ uint64_t s_p[kW];
   const uint32_t l = lane_id(), w = wave_id();
-  if (blockIdx.x >= workers) {
-    const uint32_t b = blockIdx.x - workers;
-    const uint32_t jr = b / per_dev, j = c.j0 + jr;
-    const uint32_t tb = (b - jr * per_dev) * (kW * kWriteTiles), s0 = tb + w * kWriteTiles;
-    const uint64_t row = (uint64_t)j * c.nslot;
-    const bool live = l < kWriteTiles && s0 + l < c.nslot;
-    const uint32_t va = live ? c.slot_cnt[row + s0 + l] : 0x8000u;
-    uint64_t pre;
-    if (kOwnOffsets) {
-      if (c.st[j].fallback) return;
-      static_assert(kW * kWriteTiles <= 64, "a wave scans its workgroup's tiles");
-      const uint32_t n = l < kW * kWriteTiles && tb + l < c.nslot ? c.tile_cnt[row + tb + l] : 0u;
-      const uint64_t base = tiles_before<kWB>(c, j, tb, s_p);
-      const uint64_t ex = base + wave_incl_scan_u64(counts_of(n)) - counts_of(n);
-      pre = __shfl(ex, w * kWriteTiles + (l < kWriteTiles ? l : 0u), 64);
-    } else {
-      pre = c.tile_pre[live ? row + s0 + l : row];
-      if (c.st[j].fallback) return;
-    }
-    if (ballot(!(va & 0x8000u)) == 0ull) return;
-    Out o = out_of(c, j);
-    const uint32_t shift = c.desc[j].shift;
-    for (uint32_t i = 0; i < kWriteTiles; ++i) {
-      const uint32_t v = __builtin_amdgcn_readlane(va, i);
-      if (v & 0x8000u) continue;
-      o.run_g = __builtin_amdgcn_readlane((uint32_t)pre, i);
-      o.run_e = __builtin_amdgcn_readlane((uint32_t)(pre >> 32), i);
-      o.e2 = 0.0;
-      write_staged(c, j, s0 + i, v & 0x7FFFu, (v & 0x7FFFu) - (v >> 16), shift, o);
-      const double es = wave_sum_f64(o.e2);
-      if (l == 0) c.ekept[row + s0 + i] = es;
-    }
-    return;
+  const uint32_t jr = b / per_dev, j = c.j0 + jr;
+  const uint32_t tb = (b - jr * per_dev) * (kW * kWriteTiles), s0 = tb + w * kWriteTiles;
+  const uint64_t row = (uint64_t)j * c.nslot;
+  const bool live = l < kWriteTiles && s0 + l < c.nslot;
+  const uint32_t va = live ? c.slot_cnt[row + s0 + l] : 0x8000u;
+  uint64_t pre;
+  if (kOwnOffsets) {
+    if (c.st[j].fallback) return;
+    static_assert(kW * kWriteTiles <= 64, "a wave scans its workgroup's tiles");
+    const uint32_t n = l < kW * kWriteTiles && tb + l < c.nslot ? c.tile_cnt[row + tb + l] : 0u;
+    const uint64_t base = tiles_before<kWB>(c, j, tb, s_p);
+    const uint64_t ex = base + wave_incl_scan_u64(counts_of(n)) - counts_of(n);
+    pre = __shfl(ex, w * kWriteTiles + (l < kWriteTiles ? l : 0u), 64);
+  } else {
+    pre = c.tile_pre[live ? row + s0 + l : row];
+    if (c.st[j].fallback) return;
   }
+  if (ballot(!(va & 0x8000u)) == 0ull) return;
+  Out o = out_of(c, j);
+  const uint32_t shift = c.desc[j].shift;
+  for (uint32_t i = 0; i < kWriteTiles; ++i) {
+    const uint32_t v = __builtin_amdgcn_readlane(va, i);
+    if (v & 0x8000u) continue;
+    o.run_g = __builtin_amdgcn_readlane((uint32_t)pre, i);
+    o.run_e = __builtin_amdgcn_readlane((uint32_t)(pre >> 32), i);
+    o.e2 = 0.0;
+    write_staged(c, j, s0 + i, v & 0x7FFFu, (v & 0x7FFFu) - (v >> 16), shift, o);
+    const double es = wave_sum_f64(o.e2);
+    if (l == 0) c.ekept[row + s0 + i] = es;
+  }
+}
+
+// The same over the hot tiles, every workers-th of them from the first on, one
+// per workgroup of kWB threads.
+template <int kWB, bool kOwnOffsets>
+__device__ inline void write_hot_tiles(const Ctx& c, uint32_t first, uint32_t workers, uint64_t* s_p)
+{
   __shared__ double s_e[kHotSums];
-  __shared__ uint32_t s_n[kW];
-  for_hot_tiles<true, true>(c, blockIdx.x, workers, [&](uint32_t j, uint32_t s) {
+  __shared__ uint32_t s_n[kWB / 64];
+  for_hot_tiles<true, true>(c, first, workers, [&](uint32_t j, uint32_t s) {
     const uint64_t slot = (uint64_t)j * c.nslot + s;
     const uint64_t pre = kOwnOffsets ? tiles_before<kWB>(c, j, s, s_p) : c.tile_pre[slot];
     Out o = out_of(c, j);
@@ -1421,6 +1419,22 @@ __global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(7, 8))) voi
       c.ekept[slot] = e;
     }
   });
+}
+
+// Both in one launch, the hot tiles' workgroups first: theirs is the longer work.
+// The staged tiles are bound by the latency of their slots and offsets, so the
+// waves in flight count: at 8 per SIMD and 256 threads 32 x 143.7 M take 390 us
+// from the main pass to the aggregation, at 7 and 512 threads 454, in two launches
+// (each kind its own kernel) 395 and with many hot tiles more than in one
+// (30 x 143.7 M with layers of their own scale: 4335 us per step, 4480, 4510).
+// Where a workgroup sums its own offsets 8 waves would spill.
+template <int kWB, bool kOwnOffsets>
+__global__ __launch_bounds__(kWB) __attribute__((amdgpu_waves_per_eu(kOwnOffsets ? 7 : 8, 8))) void k_write(
+    Ctx c, uint32_t workers, uint32_t per_dev)
+{
+  __shared__ uint64_t s_p[kWB / 64];
+  if (blockIdx.x >= workers) write_staged_tiles<kWB, kOwnOffsets>(c, blockIdx.x - workers, per_dev, s_p);
+  else write_hot_tiles<kWB, kOwnOffsets>(c, blockIdx.x, workers, s_p);
 }
 
 // ---- host-side launchers ---------------------------------------------------------------------
@@ -1481,16 +1495,19 @@ static void launch_post(const Ctx& c, const SelectPlan& p, hipStream_t s, int ha
     kernel<<<per_dev * c.jn + p.hot_workers, block, 0, s>>>(c, p.hot_workers, per_dev);
   };
   // A hot tile's time is its workgroup's: 16 waves where a few tiles are all
-  // there is (4 x 61,706: 11.5 us against 17), 8 else (8 x 11.2 M: 34 against 40),
-  // 4 beside a main pass, which rarely leaves 8 free at once (per-layer step of 16
-  // x 143.7 M: 2680 against 2754).
-  if (!own_offsets(c, p)) {
-    if (p.beside) write(k_write<256, false>, 256);
-    else write(k_write<512, false>, 512);
-  } else if ((uint64_t)c.jn * c.nslot <= 512) {
-    write(k_write<1024, true>, 1024);
+  // there is (4 x 61,706: 11.5 us against 17), 8 where they sum their own offsets
+  // (8 x 11.2 M: 34 against 40) or are at most 4096 in all (one of 25.6 M, 1560
+  // tiles: 134 us per step against 138), else 4 (2 x 60.2 M, 7348 tiles: 279 against
+  // 282; 16 x 25.6 M at ratio 0.1: 725 against 739), also beside a main pass, which
+  // rarely leaves 8 free at once (per-layer step of 16 x 143.7 M: 2680 against 2754).
+  const uint64_t tiles = (uint64_t)c.jn * c.nslot;
+  if (own_offsets(c, p)) {
+    if (tiles <= 512) write(k_write<1024, true>, 1024);
+    else write(k_write<512, true>, 512);
+  } else if (tiles <= 4096 && !p.beside) {
+    write(k_write<512, false>, 512);
   } else {
-    write(k_write<512, true>, 512);
+    write(k_write<256, false>, 256);
   }
   k_final<<<c.jn, kBlock, 0, s>>>(c);
 }
