@@ -251,9 +251,9 @@ bool make_layout(uint32_t K, uint64_t n, const double* ratios, bool force_exact,
       if (keys > (double)L.band_keys) L.band_keys = (uint64_t)keys;
     }
   }
-  // Blocks of the exact path's histogram passes: 8 rounds, fewer where that
-  // leaves compute units without one.
-  L.fb_rounds = 8;
+  // Blocks of the exact path's histogram passes: kFbRounds rounds, fewer where
+  // that leaves compute units without one.
+  L.fb_rounds = kFbRounds;
   while (L.fb_rounds > 1 && (uint64_t)K * ceil_div_u64(n + 3, (uint64_t)L.fb_rounds * kRound) < 512) L.fb_rounds /= 2;
   L.nfb = ceil_div_u64(n + 3, (uint64_t)L.fb_rounds * kRound);
   size_t o = 0;

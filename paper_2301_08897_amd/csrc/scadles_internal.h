@@ -29,6 +29,7 @@ constexpr int kTicketSample = 0, kTicketRefine = 1, kTicketHist = 2, kTicketFull
 constexpr uint32_t kKeyInf = 0x80000000u;   // above every 31-bit key
 constexpr uint32_t kKeyMask = 0x7FFFFFFFu;
 constexpr uint64_t kSat31 = 0x7FFFFFFFull;
+constexpr int kFbRounds = 8;           // exact path's histogram blocks: rounds per block (at most: see Ctx::fb_rounds)
 constexpr int kFullWorkers = 1024;     // grid-stride workgroups of the exact path's histogram passes
 constexpr int kHotWorkers = 4096;      // grid-stride workgroups for hot tiles
 constexpr int kBesideWorkers = 256;    // both, beside another selection's main pass
