@@ -788,13 +788,15 @@ static scadles_status run_layers(const float* const* grads, uint32_t K, const ui
                  nullptr, nullptr, nullptr, (uint32_t)off, 2u * L, ll.c, ll.p);
     ll.p.parts = 1;
     ll.p.beside = 1;
-    // few persistent workgroups: each waits for a slot the main pass leaves.
-    // Where most tiles will be hot (their slots hold 4% of the elements) theirs
-    // is the most of the work, and it takes as many as ever.
+    // Fewer workgroups for hot tiles: each waits for a slot the main pass leaves
+    // (three long layers of 8 x 50 M: 519, 524 and 535 us with 256, 1024 and 4096), but
+    // a layer that turns out hot or on the exact path needs them (8 x 20 M with
+    // entries in clusters 306, 259 and 258 us; with 99.5% zeros 1358, 921 and 863).
+    // Where most tiles will be hot (their slots hold 4% of the elements) it takes
+    // as many as ever.
     uint64_t kmax = 0;
     for (uint32_t j = 0; j < K; ++j) kmax = std::max<uint64_t>(kmax, Ll.k[j]);
-    if (kmax < nl / 32) ll.p.hot_workers = std::min<uint32_t>(ll.p.hot_workers, kBesideWorkers);
-    ll.p.full_workers = std::min<uint32_t>(ll.p.full_workers, kBesideWorkers);
+    if (kmax < nl / 32) ll.p.hot_workers = std::min<uint32_t>(ll.p.hot_workers, kBesideHotWorkers);
     ll.c.err_acc = err_acc;
   }
 

@@ -30,9 +30,9 @@ constexpr uint32_t kKeyInf = 0x80000000u;   // above every 31-bit key
 constexpr uint32_t kKeyMask = 0x7FFFFFFFu;
 constexpr uint64_t kSat31 = 0x7FFFFFFFull;
 constexpr int kFbRounds = 8;           // exact path's histogram blocks: rounds per block (at most: see Ctx::fb_rounds)
-constexpr int kFullWorkers = 1024;     // grid-stride workgroups of the exact path's histogram passes
+constexpr int kFullWorkers = 1024;     // workgroups of the exact path's histogram passes
 constexpr int kHotWorkers = 4096;      // grid-stride workgroups for hot tiles
-constexpr int kBesideWorkers = 256;    // both, beside another selection's main pass
+constexpr int kBesideHotWorkers = 1024;   // the same, beside another selection's main pass
 constexpr int kWaveCap = 512;          // main pass: candidates one wave chunk (4096 elements) can stage
 constexpr int kSlotWords = 1024;       // 32-bit words of one tile's slot region (4 KiB)
 
@@ -187,7 +187,7 @@ struct SelectPlan {
   uint32_t sample_blocks;     // sample workgroups per device
   uint64_t interval_keys;     // expected keys in [t_lo, t_hi) of all devices
   uint32_t hist_blocks;       // workgroups per device of a threshold pass over the band list
-  uint32_t full_workers;      // grid-stride workgroups of the exact path's histogram passes
+  uint32_t full_workers;      // workgroups of the exact path's histogram passes
   uint32_t hot_workers;       // grid-stride workgroups for hot tiles (all tiles of exact devices)
   uint32_t parts;             // device groups, 1 .. kMaxParts
   uint32_t beside;            // the rest runs beside other selections' main passes (small workgroups)

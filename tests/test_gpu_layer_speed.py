@@ -1,0 +1,65 @@
+"""GPU test that the selection of one layer takes no much longer than a whole
+fused step over the same gradients (selection, aggregation and update), whatever
+the values: a layer must not be left to a few workgroups because its values
+are tied, mostly zeros, unevenly spread, or kept at a high ratio. The bounds are
+wide (what they exclude took 2 to 100 times as long)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from _gpu_common import log, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sc():
+    import paper_2301_08897_amd as m
+    return m
+
+
+def gradients(torch, dev, kind, K, n):
+    g = torch.Generator(device=dev).manual_seed(11)
+    G = torch.empty(K, n, device=dev)
+    for x in G:
+        x.normal_(generator=g)
+        u = torch.empty(n, device=dev).uniform_(generator=g)
+        if kind == "zeros":
+            x.copy_(torch.where(u < 0.995, x * 0.0, x))
+        elif kind == "ties":                  # 1.5% of the elements at a magnitude near the 1% largest
+            x.copy_(torch.where(u > 0.985, torch.sign(x) * 2.5, x))
+        elif kind == "clusters":              # every eighth run of 32768 elements four times as large
+            x[(torch.arange(n, device=dev) // 32768) % 8 == 0] *= 4.0
+    return G
+
+
+def best_us(torch, run):
+    run()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(5):
+        a.record()
+        for _ in range(3):
+            run()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / 3)
+    return best
+
+
+LONG = [(20_000_000, 0.3, "normal"), (20_000_000, 0.01, "zeros"), (20_000_000, 0.01, "clusters")]
+
+
+@pytest.mark.parametrize("n,ratio,kind", LONG)
+def test_layer_against_step(sc, n, ratio, kind):
+    torch, dev = torch_dev()
+    K = 8
+    G = gradients(torch, dev, kind, K, n)
+    step = sc.FusedStep(G, [ratio] * K, params=torch.zeros(n, device=dev))
+    w = np.full(K, 1.0 / K, dtype=np.float32)
+    t_step = best_us(torch, lambda: step.run(w, 0.1))
+    layer = sc.LayerSelect(G, [0, n], [ratio] * K)
+    t_layer = best_us(torch, layer.run)
+    log(f"layer of {n}, ratio {ratio}, {kind}: {t_layer:.0f} us, step {t_step:.0f} us")
+    assert t_layer <= 1.3 * t_step
