@@ -552,7 +552,8 @@ uint64_t scadles_layers_k(const uint64_t* seg_off, uint32_t L, double ratio)
 // layer's, for layers selected by the multi-launch path) and after it the
 // row region (layer table, row descriptors, per-row energies).
 struct LayersWs {
-  size_t sel = 0, table = 0, rows = 0, row_e = 0, bst = 0, chunk = 0, cand = 0, part_e = 0, err = 0, total = 0;
+  size_t sel = 0, table = 0, rows = 0, row_e = 0, bst = 0, chunk = 0, cand = 0, part_e = 0, err = 0, slow_cnt = 0,
+         slow_list = 0, slow_hist = 0, total = 0;
 };
 
 // Parts of a split row of n elements (the virtual row [0, n + shift), shift <= 3).
@@ -573,21 +574,23 @@ static uint64_t row_wave_cap(uint64_t n, const double* ratios, uint32_t K)
   return share <= kRowWaveLen / 2 ? (share + 63) / 64 * 64 : 0;
 }
 
-// Entries of a split row's candidate list (0: the row is not split).
+// Entries of a split row's candidate list (0: the row is not split): the waves'
+// regions and a pool of half their size (2 k_max + 4096 and more) for the waves
+// with more candidates than theirs holds, so that entries in clusters fit too.
 static uint64_t row_cand_list(uint64_t n, const double* ratios, uint32_t K)
 {
-  return row_parts_of(n) * kRowPartWaves * row_wave_cap(n, ratios, K);
+  return row_parts_of(n) * kRowPartWaves * row_wave_cap(n, ratios, K) / 2 * 3;
 }
 
 // Whether a layer of n elements is selected as rows. Without the option: up to
 // 2^21 elements, and up to 2^22 while it can be split and its select workgroup
 // has room for the selection interval (12 standard deviations of the sample rank
 // and 16 ranks; a tenth for chance). A split row costs no launches of its own
-// (16 x 143.7 M with four layers of 2 to 4 M: 2620 us by the multi-launch
-// selection, 2393 as rows), but one whose interval does not fit after all, as
-// with mostly zeros, is selected by a single workgroup, whose time grows with
-// the row: hence the bound (8 devices x 8 layers of 7.5 M: 1173 and 772 us, but
-// a row of 9.6 M that did not fit 8 ms).
+// (8 devices x 8 layers of 3 M: 966 us by the multi-launch selection, 258 as rows;
+// one layer of 4.1 M 182 and 156). Values whose interval does not fit after all
+// cost the select workgroup reads of the row's list (1.5% ties: 213 and 181), those
+// whose candidates do not fit the list three more passes over the row (99.5%
+// zeros: 646 and 325). The bound of 2^22 keeps both short.
 static bool row_layer(uint64_t n, const double* ratios, uint32_t K)
 {
   const int64_t most = g_row_max.load();
@@ -631,7 +634,10 @@ static LayersWs layers_ws(uint32_t K, const uint64_t* seg_off, uint32_t L, const
   w.cand = align256(w.chunk + sizeof(uint32_t) * (size_t)kChunkWords * kRowPartChunks * parts);
   w.part_e = align256(w.cand + sizeof(uint64_t) * cands);
   w.err = align256(w.part_e + sizeof(double) * 2ull * kRowPartWaves * parts);
-  w.total = align256(w.err + sizeof(uint32_t) * K);
+  w.slow_cnt = align256(w.err + sizeof(uint32_t) * K);
+  w.slow_list = align256(w.slow_cnt + sizeof(uint64_t));
+  w.slow_hist = align256(w.slow_list + sizeof(uint32_t) * 2ull * nbig * K);
+  w.total = align256(w.slow_hist + sizeof(uint32_t) * (size_t)kBins * nbig * K);
   return w;
 }
 
@@ -705,6 +711,9 @@ static scadles_status run_layers(const float* const* grads, uint32_t K, const ui
   rc.chunk = reinterpret_cast<uint32_t*>(base + lw.chunk);
   rc.cand = reinterpret_cast<uint64_t*>(base + lw.cand);
   rc.part_e = reinterpret_cast<double*>(base + lw.part_e);
+  rc.slow_cnt = reinterpret_cast<unsigned long long*>(base + lw.slow_cnt);
+  rc.slow_list = reinterpret_cast<uint32_t*>(base + lw.slow_list);
+  rc.slow_hist = reinterpret_cast<uint32_t*>(base + lw.slow_hist);
   RowsPrep rp;
   memset(&rp, 0, sizeof(rp));
   for (uint32_t j = 0; j < K; ++j) {

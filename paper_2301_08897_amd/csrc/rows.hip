@@ -15,6 +15,7 @@
 // (a histogram read per digit until the remaining keys fit in LDS) and the
 // output positions come from a workgroup scan per round.
 #include "frame.h"
+#include "radix.h"
 
 namespace scadles {
 
@@ -126,6 +127,7 @@ __global__ __launch_bounds__(256) void k_rows_prep(RowsCtx rc, RowsPrep rp, PutA
   const uint64_t* table = put.count ? put.v : rc.table;
   if (j == 0)
     for (uint32_t i = tid; i < put.count; i += 256) put.dst[i] = put.v[i];
+  if (j == 0 && tid == 0) *rc.slow_cnt = 0ull;
   const double ratio = rp.ratio[j];
   uint64_t run = 0;
   for (uint32_t l0 = 0; l0 < rc.L; l0 += 256) {
@@ -322,30 +324,52 @@ __device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t ve
   const uint64_t stride = whole ? 256u : (uint64_t)kRowSampleStride;
   for (uint32_t i = tid; i < (1u << kRowSampleBits); i += kRowBlock) shist[i] = 0u;
   __syncthreads();
-  // visit(key) for the calling thread's keys of the sample
-  auto sample = [&](auto visit) {
-    for (uint64_t c0 = w; c0 * stride < vend; c0 += 4 * kRowWaves) {
-      f4 x[4];
+  // count(key, valid) for the calling thread's keys of the sample, 16 at a time
+  // (kAhead chunks per wave in flight: the passes are bound by their latency)
+  constexpr int kAhead = 8;
+  uint32_t s_cnt = 0;
+  auto sample = [&](auto count) {
+    s_cnt = 0;
+    for (uint64_t c0 = w; c0 * stride < vend; c0 += kAhead * kRowWaves) {
+      const uint64_t v0 = c0 * stride + 4u * lane;
+      const uint64_t step = kRowWaves * stride;
+      if (c0 * stride >= row.shift && (c0 + (kAhead - 1) * kRowWaves) * stride + 256 <= vend) {
+        // only the row's elements: plain aligned loads and no checks
+        const GLOBAL float* p = row.p + (v0 - row.shift);
+        f4 x[kAhead];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint64_t v = (c0 + r * kRowWaves) * stride + 4u * lane;
-        x[r] = v < vend ? load4(row, v, false) : f4{0.f, 0.f, 0.f, 0.f};
+        for (int r = 0; r < kAhead; ++r) x[r] = ld4(p + r * step);
+#pragma unroll
+        for (int r0 = 0; r0 < kAhead; r0 += 4) {
+          uint32_t key[16];
+#pragma unroll
+          for (int i = 0; i < 16; ++i) key[i] = key_of(x[r0 + i / 4][i % 4]);
+          count(key, 0xFFFFu);
+        }
+        s_cnt += 4 * kAhead;
+        continue;
       }
+#pragma unroll 1
+      for (int r0 = 0; r0 < kAhead; r0 += 4) {
+        uint32_t key[16], valid = 0;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint64_t v = (c0 + r * kRowWaves) * stride + 4u * lane;
+        for (int r = 0; r < 4; ++r) {
+          const uint64_t v = v0 + (r0 + r) * step;
+          const f4 x = v < vend ? load4(row, v, false) : f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (v < vend && in_row(row, v + q)) visit(key_of(x[r][q]));
+          for (int q = 0; q < 4; ++q) {
+            key[4 * r + q] = key_of(x[q]);
+            valid |= v < vend && in_row(row, v + q) ? 1u << (4 * r + q) : 0u;
+          }
+        }
+        count(key, valid);
+        s_cnt += (uint32_t)__builtin_popcount(valid);
       }
     }
   };
   constexpr int kShift = 31 - kRowSampleBits;
-  uint32_t s_cnt = 0;
-  sample([&](uint32_t key) {
-    atomicAdd(&shist[key >> kShift], 1u);
-    ++s_cnt;
-  });
+  const SelView all{0u, kKeyInf, (uint32_t)kShift, (uint32_t)kRowSampleBits, 0u};
+  sample([&](const uint32_t (&key)[16], uint32_t valid) { count_digits<true>(all, key, valid, shist); });
   uint32_t s_n;
   row_scan(s_cnt, s_w, s_n);
   // sample ranks bracketing the k-th largest key
@@ -379,10 +403,22 @@ __device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t ve
   static_assert(2 * kN <= kRowCand, "both bins' finer histograms fit the candidate array");
   for (uint32_t i = tid; i < 2 * kN; i += kRowBlock) shist[i] = 0u;
   __syncthreads();
-  sample([&](uint32_t key) {
-    const uint32_t b = key >> kShift, f = (key >> kFine) & (kN - 1u);
-    if (b == lo) atomicAdd(&shist[f], 1u);
-    if (r_hi >= 1 && b == hi) atomicAdd(&shist[kN + f], 1u);
+  const SelView in_bin_lo{0u, kKeyInf, (uint32_t)kFine, (uint32_t)kRowRefineBits, lo};
+  const SelView in_bin_hi{0u, kKeyInf, (uint32_t)kFine, (uint32_t)kRowRefineBits, hi};
+  sample([&](const uint32_t (&key)[16], uint32_t valid) {
+    // few keys lie in the two bins, but where many do (zeros, ties) they are equal
+    const uint32_t k0 = key[0] >> kShift;
+    if (__builtin_popcountll(ballot(k0 == lo)) >= (int)kTied || __builtin_popcountll(ballot(k0 == hi)) >= (int)kTied) {
+      count_digits<true>(in_bin_lo, key, valid, shist);
+      if (r_hi >= 1) count_digits<true>(in_bin_hi, key, valid, shist + kN);
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t k = key[i] >> kShift, f = (key[i] >> kFine) & (kN - 1u);
+      if (k == lo && ((valid >> i) & 1u)) atomicAdd(&shist[f], 1u);
+      if (k == hi && r_hi >= 1 && ((valid >> i) & 1u)) atomicAdd(&shist[kN + f], 1u);
+    }
   });
   if (tid == 0) s_res[0] = s_res[1] = s_res[2] = 0u;
   __syncthreads();
@@ -474,11 +510,14 @@ __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
   uint32_t t_lo, t_hi;
   row_bracket(d, row, vend, blockIdx.x < rc.Lb * rc.K, cand, s_w, s_res, t_lo, t_hi);
   if (blockIdx.x < rc.Lb * rc.K) {
+    for (uint32_t i = tid; i < (uint32_t)kBins; i += kRowBlock) rc.slow_hist[(uint64_t)blockIdx.x * kBins + i] = 0u;
     if (tid == 0) {
       BigRowState st;
       __builtin_memset(&st, 0, sizeof(st));
-      st.t_lo = t_lo;
-      st.t_hi = t_hi;
+      // t_lo = 0: every key a candidate (a row of mostly zeros); none is staged,
+      // and the row is a slow one
+      st.t_lo = t_lo ? t_lo : kKeyInf;
+      st.t_hi = t_lo ? t_hi : kKeyInf;
       rc.bst[blockIdx.x] = st;
     }
     return;
@@ -636,23 +675,29 @@ __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
 //   k_big_gather   one workgroup per part, the one read of the row: sum of
 //                  g^2 and, per chunk, the keys >= t_hi counted and the
 //                  candidates (keys >= t_lo) staged in index order in the
-//                  wave's own region of the row's candidate list;
-//   k_big_select   one workgroup per row: the selection-interval keys (the
-//                  candidates below t_hi) collected in LDS, the threshold
-//                  selected among them, then every chunk's kept entries above /
+//                  wave's own region of the row's candidate list, or, where the
+//                  row's entries lie in clusters, in a run of the row's pool;
+//   k_big_select   one workgroup per row: the threshold among the
+//                  selection-interval keys (the candidates below t_hi), collected
+//                  in LDS or, where equal keys make them too many, read from the
+//                  list digit by digit; then every chunk's kept entries above /
 //                  equal to it (counted on its candidates) and their exclusive
-//                  prefix in index order. A row whose bracket missed, or whose
-//                  candidates overflowed a wave's region, is selected and
-//                  written here, by this workgroup alone, as k_rows does it;
+//                  prefix in index order. A row whose bracket missed or reaches
+//                  down to zero, or whose pool overflowed, goes on the list of
+//                  slow rows;
 //   k_big_write    one workgroup per part: every chunk's kept entries, from its
 //                  candidates, at the positions from its prefix;
-//   k_rows_energy  the kept energy of each row from its waves' sums, in order,
-//                  then the device's.
-// No workgroup waits for another inside a launch, and the part kernels have
-// no barrier and no atomic but the rare overflow flag.
+//   k_slow_hist, k_slow_count, k_slow_write
+//                  the slow rows, by all of the GPU: three digit passes over the
+//                  rows' elements, the chunks' counts and prefixes, the output,
+//                  all read from the gradient. Without slow rows these end at once
+//                  (five launches of 4.5 us);
+//   k_rows_energy  the energies of each row from its waves' sums, in order, then
+//                  the device's.
+// No workgroup waits for another inside a launch, and the gather has no
+// barrier and no atomic but the rare waves' that do not fit their region.
 constexpr int kPartWaves = (int)kRowPartWaves;
 constexpr int kBigCand = (int)kRowBigCand;
-static_assert(kBigCand >= kRowCand, "the whole-row path of the select kernel uses kRowCand keys of the array");
 constexpr int kPartBlock = 64 * kPartWaves;
 constexpr int kWaveChunks = kRowPartChunks / kPartWaves;    // chunks of one wave, loaded at once
 static_assert(kRowChunkLen == 256u * kRowR, "a chunk is one wave's kRowR rounds");
@@ -699,21 +744,25 @@ __device__ inline void row_parts(const RowsCtx& rc, uint32_t b, uint32_t& g0, ui
   g0 = (uint32_t)(pre[q] * rc.K) + j * np;
 }
 
-// Split row b's candidate list: its first entry and the capacity of one wave's region.
-__device__ inline void row_cands(const RowsCtx& rc, uint32_t b, uint64_t& off, uint32_t& wcap)
+// Split row b's candidate list: its first entry, the capacity of one wave's
+// region and that of the pool behind the regions (half of them all).
+__device__ inline void row_cands(const RowsCtx& rc, uint32_t b, uint64_t& off, uint32_t& wcap, uint32_t& pool)
 {
   const uint64_t* pre = rc.table + 2ull * rc.L + 1;             // part_pre, then cand_pre
   const uint64_t* cpre = pre + rc.Lb + 1;
   const uint32_t q = b / rc.K, j = b - q * rc.K;
   const uint64_t per_row = cpre[q + 1] - cpre[q];
+  const uint32_t waves = (uint32_t)(pre[q + 1] - pre[q]) * kPartWaves;
   off = cpre[q] * rc.K + (uint64_t)j * per_row;
-  wcap = (uint32_t)(per_row / ((pre[q + 1] - pre[q]) * kPartWaves));
+  wcap = (uint32_t)(per_row / waves) / 3u * 2u;
+  pool = (uint32_t)(per_row - (uint64_t)waves * wcap);
 }
 
 // Fixed-order sum of n doubles by one wave (lane l adds l, l + 64, ...).
 __device__ inline double wave_sum_list(const double* a, uint32_t n)
 {
   double v = 0.0;
+#pragma unroll 4
   for (uint32_t i = lane_id(); i < n; i += 64) v += a[i];
   return wave_sum_f64(v);
 }
@@ -799,136 +848,232 @@ __global__ __launch_bounds__(kPartBlock) __attribute__((amdgpu_waves_per_eu(5, 5
   }
   const uint32_t t_lo = st->t_lo, t_hi = st->t_hi;
   uint64_t coff;
-  uint32_t wcap;
-  row_cands(rc, po.b, coff, wcap);
-  const uint32_t wbase = (po.p * kPartWaves + w) * wcap;       // the wave's region in the row's list
-  GLOBAL uint64_t* cand = gptr(rc.cand) + coff + wbase;
+  uint32_t wcap, pool;
+  row_cands(rc, po.b, coff, wcap, pool);
+  GLOBAL uint64_t* list = gptr(rc.cand) + coff;
   GLOBAL uint32_t* rec = gptr(rc.chunk) + ((uint64_t)blockIdx.x * kRowPartChunks + c0) * kChunkWords;
+  const uint32_t wbase = (po.p * kPartWaves + w) * wcap;       // the wave's region in the row's list
   double e_all = 0.0;
   uint32_t at = 0;
 #pragma unroll
   for (int c = 0; c < kWaveChunks; ++c) {
     const uint64_t vc = v0 + (uint64_t)c * kRowChunkLen;
     uint32_t nsure, ncand;
-    if (full) gather_chunk<true>(x[c], vc, vend, row, t_lo, t_hi, at, s_c[w], cand, wcap, nsure, ncand, e_all);
-    else gather_chunk<false>(x[c], vc, vend, row, t_lo, t_hi, at, s_c[w], cand, wcap, nsure, ncand, e_all);
+    if (full) gather_chunk<true>(x[c], vc, vend, row, t_lo, t_hi, at, s_c[w], list + wbase, wcap, nsure, ncand, e_all);
+    else gather_chunk<false>(x[c], vc, vend, row, t_lo, t_hi, at, s_c[w], list + wbase, wcap, nsure, ncand, e_all);
     if (lane == 0) {
       const u4 w4 = {nsure, ncand - nsure, wbase + at, ncand};
       *reinterpret_cast<GLOBAL u4*>(rec + c * kChunkWords) = w4;
     }
     at += ncand;
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // other lanes' entries
-  const uint32_t staged = at < kGatherStage ? (at < wcap ? at : wcap) : (wcap < kGatherStage ? wcap : kGatherStage);
-  for (uint32_t e = lane; e < staged; e += 64) cand[e] = s_c[w][e];
-  if (at > wcap && lane == 0) __hip_atomic_fetch_or(&st->ovf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (at <= wcap) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // other lanes' entries
+    const uint32_t staged = at < kGatherStage ? at : kGatherStage;
+    for (uint32_t e = lane; e < staged; e += 64) list[wbase + e] = s_c[w][e];
+  } else {
+    // more candidates than the region holds: all of them, read once more, to a run of
+    // the row's pool
+    uint32_t pos = 0;
+    if (lane == 0) pos = __hip_atomic_fetch_add(&st->pool, at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    pos = (uint32_t)__builtin_amdgcn_readfirstlane(pos);
+    if (pos > pool || pool - pos < at) {
+      if (lane == 0) __hip_atomic_fetch_or(&st->ovf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      uint32_t to = po.np * kPartWaves * wcap + pos;
+#pragma unroll 1
+      for (int r = 0; r < kWaveChunks * kRowR; ++r) {
+        if (r % kRowR == 0 && lane == 0) rec[(r / kRowR) * kChunkWords + 2] = to;
+        const uint64_t v = v0 + r * 256u;
+        const f4 y = v < vend ? load4(row, v, false) : f4{0.f, 0.f, 0.f, 0.f};
+        bool f[4];
+        uint64_t m[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f[q] = v < vend && in_row(row, v + q) && key_of(y[q]) >= t_lo;
+          m[q] = ballot(f[q]);
+        }
+        uint32_t cp = to + mbcnt(m[0]) + mbcnt(m[1]) + mbcnt(m[2]) + mbcnt(m[3]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (f[q])
+            list[cp++] = (uint64_t)(uint32_t)(v + q - row.shift) | ((uint64_t)__float_as_uint(y[q]) << 32);
+        to += (uint32_t)(__builtin_popcountll(m[0]) + __builtin_popcountll(m[1]) + __builtin_popcountll(m[2]) +
+                         __builtin_popcountll(m[3]));
+      }
+    }
+  }
   const double e = wave_sum_f64(e_all);
   if (lane == 0) rc.part_e[(uint64_t)blockIdx.x * kPartWaves + w] = e;
 }
 
+// Calls visit(key, valid) for the n staged keys of the lane's chunk, from the list's
+// entry `at` on, as many times in every lane of the wave: a chunk per lane, eight
+// keys loaded at once. (A window of lanes per chunk loads fewer lines but takes
+// more instructions: k_big_select of 8 devices' rows of up to 2.4 M 73 us against 34.)
+typedef uint32_t u4u __attribute__((ext_vector_type(4), aligned(8)));    // two list entries
+template <class Visit>
+__device__ inline void walk_staged(const GLOBAL uint64_t* list, uint32_t at, uint32_t n, Visit visit)
+{
+  for (uint32_t e0 = 0; ballot(e0 < n); e0 += 8) {
+    u4u kv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      // (an odd last one comes with the entry behind it; the workspace goes on there)
+      const uint32_t e = e0 + 2 * i < n ? at + e0 + 2 * i : 0u;
+      kv[i] = *reinterpret_cast<const GLOBAL u4u*>(list + e);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) visit(kv[i / 2][2 * (i % 2) + 1] & kKeyMask, e0 + i < n);
+  }
+}
+
+// Wave w takes a run of the row's 64-chunk groups, lane l chunk l of the group.
 __global__ __launch_bounds__(kRowBlock) void k_big_select(RowsCtx rc)
 {
   __shared__ uint32_t hist[kRowBins];
   __shared__ uint32_t cand[kBigCand];
-  __shared__ uint32_t s_w[kRowWaves];
+  __shared__ uint32_t s_w[2 * kRowWaves];
   __shared__ uint32_t s_res[4];
-  __shared__ double s_d[kRowWaves];
-  const uint32_t b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+  const uint32_t b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = wave_id();
   const RowDesc d = rc.rows[b];
-  GLOBAL BigRowState* st = gptr(rc.bst) + b;
+  BigRowState* st = rc.bst + b;
   uint32_t g0, np;
   row_parts(rc, b, g0, np);
   uint64_t coff;
-  uint32_t wcap;
-  row_cands(rc, b, coff, wcap);
+  uint32_t wcap, pool;
+  row_cands(rc, b, coff, wcap, pool);
   const GLOBAL uint64_t* list = gptr(rc.cand) + coff;
   const uint32_t nch = np * kRowPartChunks;
   GLOBAL uint32_t* ch = gptr(rc.chunk) + (uint64_t)g0 * kRowPartChunks * kChunkWords;
-  const Row row{gptr(d.grad), ((uint64_t)d.grad >> 2) & 3u, d.n};
-  const uint64_t vend = (uint64_t)d.n + row.shift;
-  const uint32_t t_hi = st->t_hi;
-  if (w == 0) {
-    const double ea = wave_sum_list(rc.part_e + (uint64_t)g0 * kPartWaves, np * kPartWaves);
-    if (lane == 0) rc.row_e[2ull * d.eslot] = ea;
-  }
-  // each thread a run of consecutive chunks (one chunk per thread for rows up
-  // to kRowBlock chunks); their records stay in registers for the first run
-  const uint32_t per = (nch + kRowBlock - 1) / kRowBlock;
-  const uint32_t c0 = tid * per < nch ? tid * per : nch, c1 = c0 + per < nch ? c0 + per : nch;
-  uint32_t sure = 0, band = 0;
-  for (uint32_t c = c0; c < c1; ++c) {
-    sure += ch[kChunkWords * c];
-    band += ch[kChunkWords * c + 1];
-  }
-  uint32_t sure_all, nband;
-  row_scan(sure, s_w, sure_all);
-  const uint32_t boff = row_scan(band, s_w, nband) - band;   // the thread's chunks' keys start here in LDS
-  const bool in_band = st->ovf == 0u && sure_all < d.k && d.k - sure_all <= nband && nband <= (uint32_t)kBigCand;
-  if (in_band) {
-    // the selection-interval keys (the candidates below t_hi) into LDS, each
-    // thread's chunks in order from boff: the only read of the candidates
-    uint32_t pos = boff;
-    for (uint32_t c = c0; c < c1; ++c) {
-      const uint32_t at = ch[kChunkWords * c + 2], n = ch[kChunkWords * c + 3];
-      for (uint32_t e0 = 0; e0 < n; e0 += 8) {
-        uint32_t kv[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) kv[i] = e0 + i < n ? (uint32_t)(list[at + e0 + i] >> 32) & kKeyMask : kKeyInf;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (kv[i] < t_hi) {
-            if (pos < (uint32_t)kBigCand) cand[pos] = kv[i];
-            ++pos;
-          }
-      }
+  const uint32_t t_lo = st->t_lo, t_hi = st->t_hi;
+  const uint32_t groups = (nch + 63) / 64, per = (groups + kRowWaves - 1) / kRowWaves;
+  const uint32_t q0 = w * per < groups ? w * per : groups, q1 = q0 + per < groups ? q0 + per : groups;
+  auto record = [&](uint32_t q) {
+    const uint32_t c = q * 64 + lane;
+    return c < nch ? *reinterpret_cast<const GLOBAL u4*>(ch + kChunkWords * c) : u4{0u, 0u, 0u, 0u};
+  };
+  // sums of two values per lane over the workgroup's waves: the waves before and all
+  auto wave_totals = [&](uint32_t x, uint32_t y, uint32_t& xb, uint32_t& yb, uint32_t& xa, uint32_t& ya) {
+    const uint32_t xi = wave_incl_scan(x), yi = wave_incl_scan(y);
+    __syncthreads();
+    if (lane == 63) {
+      s_w[w] = xi;
+      s_w[kRowWaves + w] = yi;
     }
     __syncthreads();
-    uint32_t need = d.k - sure_all;
-    const uint32_t thr = row_select_lds(cand, nband, need, hist, s_w, s_res);
-    // every chunk's kept entries above / equal to the threshold (its keys >=
-    // t_hi and its band keys in LDS), then their exclusive prefix in index order
-    uint32_t gsum = 0, esum = 0;
-    pos = boff;
-    for (uint32_t c = c0; c < c1; ++c) {
-      const uint32_t nb = ch[kChunkWords * c + 1];
-      uint32_t g = ch[kChunkWords * c], e = 0;
-      for (uint32_t i = 0; i < nb; ++i) {
-        const uint32_t key = cand[pos + i];
+    xb = yb = xa = ya = 0;
+    for (uint32_t i = 0; i < (uint32_t)kRowWaves; ++i) {
+      const uint32_t u = s_w[i], v = s_w[kRowWaves + i];
+      xb += i < w ? u : 0u;
+      yb += i < w ? v : 0u;
+      xa += u;
+      ya += v;
+    }
+  };
+  uint32_t sure = 0, band = 0;
+  for (uint32_t q = q0; q < q1; ++q) {
+    const u4 r = record(q);
+    sure += r[0];
+    band += r[1];
+  }
+  uint32_t sure_b, band_b, sure_all, nband;
+  wave_totals(sure, band, sure_b, band_b, sure_all, nband);
+  if (st->ovf || sure_all >= d.k || d.k - sure_all > nband) {
+    if (tid == 0) {
+      // its place in the list of slow rows and its first part among theirs, at once
+      const unsigned long long at = atomicAdd(rc.slow_cnt, (1ull << 32) | np);
+      rc.slow_list[2 * (uint32_t)(at >> 32)] = b;
+      rc.slow_list[2 * (uint32_t)(at >> 32) + 1] = (uint32_t)at;
+      st->slow = 1u;
+    }
+    return;
+  }
+  const bool in_lds = nband <= (uint32_t)kBigCand;
+  uint32_t need = d.k - sure_all, thr;
+  if (in_lds) {
+    // the selection-interval keys, chunk after chunk
+    uint32_t off = band_b;
+    for (uint32_t q = q0; q < q1; ++q) {
+      const u4 r = record(q);
+      const uint32_t incl = wave_incl_scan(r[1]), start = off + incl - r[1];
+      uint32_t pos = start;
+      walk_staged(list, r[2], r[3], [&](uint32_t key, bool valid) {
+        if (valid && key < t_hi) {
+          if (pos < (uint32_t)kBigCand) cand[pos] = key;
+          ++pos;
+        }
+      });
+      off += (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+    }
+    __syncthreads();
+    thr = row_select_lds(cand, nband, need, hist, s_w, s_res);
+  } else {
+    // too many (equal keys, which no bracket tells apart): digit by digit from the list
+    Sel sel = first_sel(t_lo, t_hi, need);
+    while (sel.bits) {
+      const SelView v = view_of(sel);
+      for (uint32_t i = tid; i < kRowBins; i += kRowBlock) hist[i] = 0u;
+      if (tid == 0) s_res[0] = s_res[1] = s_res[2] = 0u;
+      __syncthreads();
+      for (uint32_t q = q0; q < q1; ++q) {
+        const u4 r = record(q);
+        walk_staged(list, r[2], r[3], [&](uint32_t key, bool valid) { count_digit<false>(v, key, valid, hist); });
+      }
+      __syncthreads();
+      row_select_bin(hist, v.width, need, s_w, s_res);
+      need -= s_res[1];
+      sel.prefix = (sel.prefix << v.width) | s_res[0];
+      sel.bits -= v.width;
+      __syncthreads();
+    }
+    thr = sel.lo + sel.prefix;
+  }
+  // every chunk's kept entries above / equal to the threshold, in its record, then
+  // their exclusive prefix in index order
+  uint32_t gsum = 0, esum = 0, off = band_b;
+  for (uint32_t q = q0; q < q1; ++q) {
+    const u4 r = record(q);
+    uint32_t g = r[0], e = 0;
+    if (in_lds) {
+      const uint32_t incl = wave_incl_scan(r[1]), start = off + incl - r[1];
+      for (uint32_t i = 0; i < r[1]; ++i) {
+        const uint32_t key = cand[start + i];
         g += key > thr ? 1u : 0u;
         e += key == thr ? 1u : 0u;
       }
-      pos += nb;
+      off += (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+    } else {
+      walk_staged(list, r[2], r[3], [&](uint32_t key, bool valid) {
+        g += valid && key < t_hi && key > thr ? 1u : 0u;
+        e += valid && key == thr ? 1u : 0u;
+      });
+    }
+    const uint32_t c = q * 64 + lane;
+    if (c < nch) {
       ch[kChunkWords * c] = g;
       ch[kChunkWords * c + 1] = e;
-      gsum += g;
-      esum += e;
     }
-    uint32_t tg, te;
-    uint32_t rg = row_scan(gsum, s_w, tg) - gsum;
-    uint32_t re = row_scan(esum, s_w, te) - esum;
-    for (uint32_t c = c0; c < c1; ++c) {
-      const uint32_t g = ch[kChunkWords * c], e = ch[kChunkWords * c + 1];
-      ch[kChunkWords * c] = rg;
-      ch[kChunkWords * c + 1] = re;
-      rg += g;
-      re += e;
+    gsum += g;
+    esum += e;
+  }
+  uint32_t rg, re, tg, te;
+  wave_totals(gsum, esum, rg, re, tg, te);
+  for (uint32_t q = q0; q < q1; ++q) {
+    const uint32_t c = q * 64 + lane;                // the lane's own stores above
+    const uint32_t g = c < nch ? ch[kChunkWords * c] : 0u, e = c < nch ? ch[kChunkWords * c + 1] : 0u;
+    const uint32_t gi = wave_incl_scan(g), ei = wave_incl_scan(e);
+    if (c < nch) {
+      ch[kChunkWords * c] = rg + gi - g;
+      ch[kChunkWords * c + 1] = re + ei - e;
     }
-    if (tid == 0) {
-      st->thr = thr;
-      st->need = need;
-      st->slow = 0u;
-    }
-  } else {
-    // the bracket missed or a wave's candidates overflowed: this workgroup
-    // selects and writes the row on its own
-    uint32_t need = d.k;
-    const uint32_t thr = row_select_global(row, vend, need, hist, cand, s_w, s_res);
-    const double ek =
-        row_sum_f64(row_write_ordered(d, row, vend, thr, need, gptr(d.idx_out), gptr(d.val_out), s_w), s_d);
-    if (tid == 0) {
-      rc.row_e[2ull * d.eslot + 1] = ek;
-      st->slow = 1u;
-    }
+    rg += (uint32_t)__builtin_amdgcn_readlane(gi, 63);
+    re += (uint32_t)__builtin_amdgcn_readlane(ei, 63);
+  }
+  if (tid == 0) {
+    st->thr = thr;
+    st->need = need;
+    st->slow = 0u;
   }
 }
 
@@ -975,28 +1120,262 @@ __global__ __launch_bounds__(kPartBlock) void k_big_write(RowsCtx rc)
   const PartOf po = part_of(rc, blockIdx.x);
   const GLOBAL BigRowState* st = gptr(rc.bst) + po.b;
   const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+  if (st->slow) return;                         // k_slow_write's
   double e_kept = 0.0;
-  if (!st->slow) {
-    const RowDesc d = rc.rows[po.b];
-    const uint32_t thr = st->thr, need = st->need;
-    uint64_t coff;
-    uint32_t wcap;
-    row_cands(rc, po.b, coff, wcap);
-    const GLOBAL uint64_t* list = gptr(rc.cand) + coff;
-    const GLOBAL uint32_t* rec = gptr(rc.chunk) + (uint64_t)blockIdx.x * kRowPartChunks * kChunkWords;
-    GLOBAL uint32_t* oi = gptr(d.idx_out);
-    GLOBAL float* ov = gptr(d.val_out);
+  const RowDesc d = rc.rows[po.b];
+  const uint32_t thr = st->thr, need = st->need;
+  uint64_t coff;
+  uint32_t wcap, pool;
+  row_cands(rc, po.b, coff, wcap, pool);
+  const GLOBAL uint64_t* list = gptr(rc.cand) + coff;
+  const GLOBAL uint32_t* rec = gptr(rc.chunk) + (uint64_t)blockIdx.x * kRowPartChunks * kChunkWords;
+  GLOBAL uint32_t* oi = gptr(d.idx_out);
+  GLOBAL float* ov = gptr(d.val_out);
 #pragma unroll
-    for (int c = 0; c < kWaveChunks; ++c) {
-      const u4 r4 = *reinterpret_cast<const GLOBAL u4*>(rec + (w * kWaveChunks + c) * kChunkWords);
-      if (r4[3]) write_staged(list + r4[2], r4[3], d.base, thr, need, d.k, oi, ov, r4[0], r4[1], e_kept);
-    }
+  for (int c = 0; c < kWaveChunks; ++c) {
+    const u4 r4 = *reinterpret_cast<const GLOBAL u4*>(rec + (w * kWaveChunks + c) * kChunkWords);
+    if (r4[3]) write_staged(list + r4[2], r4[3], d.base, thr, need, d.k, oi, ov, r4[0], r4[1], e_kept);
   }
   const double e = wave_sum_f64(e_kept);
   if (lane == 0) rc.part_e[((uint64_t)rc.nparts + blockIdx.x) * kPartWaves + w] = e;
 }
 
-// Per device: the kept energies of its split rows (a wave per row), then the
+// ---- slow rows -----------------------------------------------------------------------------
+// The rows on the list (in the order their select workgroups came, which no
+// result depends on) are selected over all of their elements by `gridDim.x`
+// workgroups, each a run of their parts, row after row. A row's part that a
+// workgroup holds is closed by its ticket; the one that completes a row's parts
+// decides the digit or forms the chunks' prefixes.
+constexpr uint32_t kSlowWorkers = 1024;
+constexpr int kPartRounds = (int)(kRowPartLen / kRound);
+static_assert(kPartBlock == kBlock, "the slow rows' workgroups are those of the digit helpers");
+
+struct SlowRow {
+  uint32_t b, first, np;      // row, its first part among the slow rows', its parts
+  uint32_t g0;                // its first part workgroup
+};
+
+// The slow row that holds part `it` of the slow rows' parts (n of them).
+__device__ inline SlowRow slow_row(const RowsCtx& rc, uint32_t n, uint32_t it)
+{
+  const uint32_t l = lane_id();
+  uint32_t i = 0;
+  for (uint32_t i0 = 0; i0 < n; i0 += 64) {
+    const uint32_t c = (uint32_t)__builtin_popcountll(ballot(i0 + l < n && rc.slow_list[2 * (i0 + l < n ? i0 + l : 0u) + 1] <= it));
+    i += c;
+    if (c < 64) break;
+  }
+  i = (uint32_t)__builtin_amdgcn_readfirstlane(i) - 1u;       // the first row's parts start at 0
+  SlowRow r;
+  r.b = rc.slow_list[2 * i];
+  r.first = rc.slow_list[2 * i + 1];
+  row_parts(rc, r.b, r.g0, r.np);
+  return r;
+}
+
+// Calls open(row, desc), part(p) for its parts and close(row, parts done) for the
+// workgroup's run of the slow rows' parts.
+template <class Open, class Part, class Close>
+__device__ inline void for_slow_parts(const RowsCtx& rc, Open open, Part part, Close close)
+{
+  const unsigned long long cnt = *rc.slow_cnt;
+  const uint32_t items = (uint32_t)cnt, n = (uint32_t)(cnt >> 32);
+  const uint32_t it1 = (uint32_t)((uint64_t)items * (blockIdx.x + 1) / gridDim.x);
+  uint32_t it = (uint32_t)((uint64_t)items * blockIdx.x / gridDim.x);
+  while (it < it1) {
+    const SlowRow r = slow_row(rc, n, it);
+    const uint32_t end = r.first + r.np < it1 ? r.first + r.np : it1, done = end - it;
+    open(r);
+    for (; it < end; ++it) part(r, it - r.first);
+    close(r, done);
+  }
+}
+
+// Digit pass `pass` over the slow rows.
+__global__ __launch_bounds__(kBlock) void k_slow_hist(RowsCtx rc, uint32_t pass)
+{
+  __shared__ uint32_t h[kBins];
+  __shared__ uint32_t s_w[kWaves + 3];
+  Sel sel{};
+  SelView sv{};
+  Row row{};
+  for_slow_parts(
+      rc,
+      [&](const SlowRow& r) {
+        const RowDesc& d = rc.rows[r.b];
+        sel = pass == 0 ? first_sel(0u, kKeyInf, d.k) : rc.bst[r.b].sel;
+        sv = view_of(sel);
+        row = Row{gptr(d.grad), ((uint64_t)d.grad >> 2) & 3u, d.n};
+        for (int i = threadIdx.x; i < kBins; i += kBlock) h[i] = 0u;
+        __syncthreads();
+      },
+      [&](const SlowRow&, uint32_t p) {
+        const uint64_t vbase = (uint64_t)p * kRowPartLen;
+        const bool inside = vbase >= row.shift && vbase + kRowPartLen <= row.shift + row.n;
+#pragma unroll 1
+        for (int r0 = 0; r0 < kPartRounds; r0 += 4) {
+          f4 x[4];
+          uint32_t valid = 0xFFFFu;
+          if (inside) {
+            const GLOBAL float* g = row.p + (vbase - row.shift) + threadIdx.x * 4;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = ld4(g + (r0 + r) * kRound);
+          } else {
+            valid = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const uint64_t v = vbase + (uint64_t)(r0 + r) * kRound + threadIdx.x * 4;
+              x[r] = load4(row, v, false);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) valid |= in_row(row, v + e) ? 1u << (4 * r + e) : 0u;
+            }
+          }
+          uint32_t key[16];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) key[e] = key_of(x[e / 4][e % 4]);
+          count_digits<true>(sv, key, valid, h);
+        }
+      },
+      [&](const SlowRow& r, uint32_t done) {
+        __syncthreads();
+        BigRowState& st = rc.bst[r.b];
+        uint32_t* g = rc.slow_hist + (uint64_t)r.b * kBins;
+        flush_hist(h, g, kBins);
+        if (block_is_last(&st.ticket[pass], done, r.np)) {
+          decide_digit(sel, g, h, s_w);
+          if (threadIdx.x == 0) {
+            st.sel = sel;
+            st.thr = sel.result;
+            st.need = (uint32_t)sel.rank;
+          }
+        }
+        __syncthreads();
+      });
+}
+
+// A slow row's chunk c by one wave: its rounds to visit(round's elements, position).
+template <class Visit>
+__device__ inline void walk_row_chunk(const Row& row, uint64_t vend, uint64_t v0, Visit visit)
+{
+  f4 x[kRowR];
+#pragma unroll
+  for (int r = 0; r < kRowR; ++r) {
+    const uint64_t v = v0 + r * 256u;
+    x[r] = v < vend ? load4(row, v, false) : f4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int r = 0; r < kRowR; ++r) {
+    visit(x[r], v0 + r * 256u);
+    __builtin_amdgcn_sched_barrier(0);    // keep rounds apart: bounds the live ballot masks
+  }
+}
+
+// The chunks' entries above / equal to the threshold and their prefixes.
+__global__ __launch_bounds__(kBlock) void k_slow_count(RowsCtx rc)
+{
+  __shared__ uint32_t s_t[2 * kWaves];
+  const uint32_t lane = lane_id(), w = wave_id();
+  Row row{};
+  uint64_t vend = 0;
+  uint32_t thr = 0;
+  for_slow_parts(
+      rc,
+      [&](const SlowRow& r) {
+        const RowDesc& d = rc.rows[r.b];
+        row = Row{gptr(d.grad), ((uint64_t)d.grad >> 2) & 3u, d.n};
+        vend = (uint64_t)d.n + row.shift;
+        thr = rc.bst[r.b].thr;
+      },
+      [&](const SlowRow& r, uint32_t p) {
+        uint32_t* rec = rc.chunk + (uint64_t)(r.g0 + p) * kRowPartChunks * kChunkWords;
+        for (uint32_t c = w * kWaveChunks; c < (w + 1) * kWaveChunks; ++c) {
+          uint32_t g = 0, e = 0;
+          walk_row_chunk(row, vend, (uint64_t)p * kRowPartLen + (uint64_t)c * kRowChunkLen + 4u * lane,
+                         [&](const f4& x, uint64_t v) {
+#pragma unroll
+                           for (int q = 0; q < 4; ++q) {
+                             const bool valid = v < vend && in_row(row, v + q);
+                             const uint32_t key = key_of(x[q]);
+                             g += (uint32_t)__builtin_popcountll(ballot(valid && key > thr));
+                             e += (uint32_t)__builtin_popcountll(ballot(valid && key == thr));
+                           }
+                         });
+          if (lane == 0) {
+            put(rec + kChunkWords * c, g);
+            put(rec + kChunkWords * c + 1, e);
+          }
+        }
+      },
+      [&](const SlowRow& r, uint32_t done) {
+        BigRowState& st = rc.bst[r.b];
+        if (!block_is_last(&st.ticket[kSlowCountTicket], done, r.np)) return;
+        // each thread a run of consecutive chunks
+        uint32_t* ch = rc.chunk + (uint64_t)r.g0 * kRowPartChunks * kChunkWords;
+        const uint32_t nch = r.np * kRowPartChunks, per = (nch + kBlock - 1) / kBlock;
+        const uint32_t c0 = threadIdx.x * per < nch ? threadIdx.x * per : nch, c1 = c0 + per < nch ? c0 + per : nch;
+        uint32_t g = 0, e = 0;
+        for (uint32_t c = c0; c < c1; ++c) {
+          g += get(ch + kChunkWords * c);
+          e += get(ch + kChunkWords * c + 1);
+        }
+        const uint32_t gi = wave_incl_scan(g), ei = wave_incl_scan(e);
+        if (lane == 63) {
+          s_t[w] = gi;
+          s_t[kWaves + w] = ei;
+        }
+        __syncthreads();
+        uint32_t rg = gi - g, re = ei - e;
+        for (uint32_t i = 0; i < w; ++i) {
+          rg += s_t[i];
+          re += s_t[kWaves + i];
+        }
+        for (uint32_t c = c0; c < c1; ++c) {
+          const uint32_t cg = get(ch + kChunkWords * c), ce = get(ch + kChunkWords * c + 1);
+          ch[kChunkWords * c] = rg;
+          ch[kChunkWords * c + 1] = re;
+          rg += cg;
+          re += ce;
+        }
+        __syncthreads();
+      });
+}
+
+// The slow rows' kept entries.
+__global__ __launch_bounds__(kBlock) void k_slow_write(RowsCtx rc)
+{
+  const uint32_t lane = lane_id(), w = wave_id();
+  RowDesc d{};
+  Row row{};
+  uint64_t vend = 0;
+  uint32_t thr = 0, need = 0;
+  for_slow_parts(
+      rc,
+      [&](const SlowRow& r) {
+        d = rc.rows[r.b];
+        row = Row{gptr(d.grad), ((uint64_t)d.grad >> 2) & 3u, d.n};
+        vend = (uint64_t)d.n + row.shift;
+        thr = rc.bst[r.b].thr;
+        need = rc.bst[r.b].need;
+      },
+      [&](const SlowRow& r, uint32_t p) {
+        const uint32_t* rec = rc.chunk + (uint64_t)(r.g0 + p) * kRowPartChunks * kChunkWords;
+        GLOBAL uint32_t* oi = gptr(d.idx_out);
+        GLOBAL float* ov = gptr(d.val_out);
+        double e2 = 0.0;
+        for (uint32_t c = w * kWaveChunks; c < (w + 1) * kWaveChunks; ++c) {
+          uint32_t rg = rec[kChunkWords * c], re = rec[kChunkWords * c + 1];
+          walk_row_chunk(row, vend, (uint64_t)p * kRowPartLen + (uint64_t)c * kRowChunkLen + 4u * lane,
+                         [&](const f4& x, uint64_t v) {
+                           row_write_round(x, v, vend, row, d.base, thr, need, d.k, oi, ov, rg, re, e2);
+                         });
+        }
+        const double e = wave_sum_f64(e2);
+        if (lane == 0) rc.part_e[((uint64_t)rc.nparts + r.g0 + p) * kPartWaves + w] = e;
+      },
+      [](const SlowRow&, uint32_t) {});
+}
+
+// Per device: the energies of its split rows (a wave per row), then the
 // energies of all its layers, short and long (each lane a strided subset in
 // layer order, then the lanes in a fixed tree).
 constexpr int kEnergyBlock = 1024;
@@ -1005,11 +1384,14 @@ __global__ __launch_bounds__(kEnergyBlock) void k_rows_energy(RowsCtx rc, double
   const uint32_t j = blockIdx.x, lane = lane_id();
   for (uint32_t q = threadIdx.x >> 6; q < rc.Lb; q += kEnergyBlock / 64) {
     const uint32_t b = q * rc.K + j;
-    if (rc.bst[b].slow) continue;               // the select kernel wrote the row and its energy
     uint32_t g0, np;
     row_parts(rc, b, g0, np);
+    const double ea = wave_sum_list(rc.part_e + (uint64_t)g0 * kPartWaves, np * kPartWaves);
     const double ek = wave_sum_list(rc.part_e + ((uint64_t)rc.nparts + g0) * kPartWaves, np * kPartWaves);
-    if (lane == 0) rc.row_e[2ull * rc.rows[b].eslot + 1] = ek;
+    if (lane == 0) {
+      rc.row_e[2ull * rc.rows[b].eslot] = ea;
+      rc.row_e[2ull * rc.rows[b].eslot + 1] = ek;
+    }
   }
   __syncthreads();
   if (threadIdx.x >= 64) return;
@@ -1069,6 +1451,10 @@ hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* ta
     k_big_gather<<<rc.nparts, kPartBlock, 0, s>>>(rc);
     k_big_select<<<rc.Lb * rc.K, kRowBlock, 0, s>>>(rc);
     k_big_write<<<rc.nparts, kPartBlock, 0, s>>>(rc);
+    const uint32_t workers = rc.nparts < kSlowWorkers ? rc.nparts : kSlowWorkers;
+    for (uint32_t pass = 0; pass < kSlowPasses; ++pass) k_slow_hist<<<workers, kBlock, 0, s>>>(rc, pass);
+    k_slow_count<<<workers, kBlock, 0, s>>>(rc);
+    k_slow_write<<<workers, kBlock, 0, s>>>(rc);
   }
   if (rc.Ls > 0 && energies) k_rows_energy<<<rc.K, kEnergyBlock, 0, s>>>(rc, energies);
   return hipGetLastError();

@@ -262,15 +262,21 @@ constexpr uint32_t kRowBigCand = 32768;
 constexpr uint32_t kRowSampleEvery = 16;    // a row's sample: one in this many elements
 constexpr uint32_t kChunkWords = 4;         // words of a chunk's record
 
-// Per split row: its bracket, whether some wave's candidates overflowed their
-// region, and the outcome of its threshold selection.
+// Per split row: its bracket, the entries of its pool in use (the waves' whose
+// candidates overflowed their region), whether the pool overflowed, and the
+// outcome of its threshold selection.
+constexpr uint32_t kSlowPasses = 3;         // digits of 31-bit keys
+constexpr uint32_t kSlowCountTicket = kSlowPasses;
 struct BigRowState {
   uint32_t t_lo, t_hi;    // bracket of the sampled selection
-  uint32_t ovf;           // nonzero: a wave had more candidates than its region holds
-  uint32_t slow;          // 1: the select kernel wrote the row on its own (bracket missed or ovf)
+  uint32_t pool;          // entries reserved in the row's pool
+  uint32_t ovf;           // nonzero: some candidates were not staged
+  uint32_t slow;          // 1: on the list of slow rows
   uint32_t thr;           // threshold key and the number of keys equal to it that are kept
   uint32_t need;
-  uint32_t pad[2];
+  uint32_t pad;
+  uint32_t ticket[kSlowPasses + 1];   // parts done of the slow rows' digit passes and counts
+  Sel sel;                // of a slow row's threshold
 };
 
 struct RowsCtx {
@@ -284,16 +290,20 @@ struct RowsCtx {
   // part_pre[q]) + p of the part kernels; its chunks are kRowPartChunks
   // records of `chunk` from that number times kRowPartChunks on. The row's
   // candidates are staged from cand_pre[q] * K + j * (cand_pre[q + 1] -
-  // cand_pre[q]) of `cand` on, in a region of equal size per wave of its parts.
+  // cand_pre[q]) of `cand` on, in a region of equal size per wave of its parts
+  // and a pool of half their size behind them.
   uint32_t Lb;
   uint32_t nparts;        // part workgroups of all split rows
   BigRowState* bst;       // [Lb x K]
-  uint32_t* chunk;        // [nparts x kRowPartChunks x kChunkWords]: per chunk, keys >= t_hi, 0, where
-                          // its candidates start in the row's region, their number; after the
-                          // selection the first two are the kept entries above / equal to the
-                          // threshold before the chunk
+  uint32_t* chunk;        // [nparts x kRowPartChunks x kChunkWords]: per chunk, keys >= t_hi, keys of the
+                          // selection interval, where its candidates start in the row's list, their
+                          // number; after the selection the first two are the kept entries above /
+                          // equal to the threshold before the chunk
   uint64_t* cand;         // staged candidates: index | value bits << 32, in index order per chunk
   double* part_e;         // [2 x nparts x 4] E_all, then E_kept, partial sums per wave of each part
+  unsigned long long* slow_cnt;   // slow rows << 32 | their parts
+  uint32_t* slow_list;    // [Lb x K x 2]: row, its first part among the slow rows'
+  uint32_t* slow_hist;    // [Lb x K x kBins] a slow row's digit
 };
 
 

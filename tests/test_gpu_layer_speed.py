@@ -27,8 +27,8 @@ def gradients(torch, dev, kind, K, n):
         u = torch.empty(n, device=dev).uniform_(generator=g)
         if kind == "zeros":
             x.copy_(torch.where(u < 0.995, x * 0.0, x))
-        elif kind == "ties":                  # 1.5% of the elements at a magnitude near the 1% largest
-            x.copy_(torch.where(u > 0.985, torch.sign(x) * 2.5, x))
+        elif kind == "ties":                  # 1.5% of the elements at a magnitude that 0.5% of the others exceed
+            x.copy_(torch.where(u > 0.985, torch.sign(x) * 2.807, x))
         elif kind == "clusters":              # every eighth run of 32768 elements four times as large
             x[(torch.arange(n, device=dev) // 32768) % 8 == 0] *= 4.0
     return G
@@ -48,11 +48,14 @@ def best_us(torch, run):
     return best
 
 
-LONG = [(20_000_000, 0.3, "normal"), (20_000_000, 0.01, "zeros"), (20_000_000, 0.01, "clusters")]
+# a long layer by the multi-launch selection; one that is a row by default
+LONG = [(20_000_000, 0.3, "normal", 1.3), (20_000_000, 0.01, "zeros", 1.3), (20_000_000, 0.01, "clusters", 1.3)]
+ROW = [(4_100_000, 0.01, "normal", 3.0), (4_100_000, 0.01, "ties", 3.0), (4_100_000, 0.01, "zeros", 3.0),
+       (4_100_000, 0.01, "clusters", 3.0)]
 
 
-@pytest.mark.parametrize("n,ratio,kind", LONG)
-def test_layer_against_step(sc, n, ratio, kind):
+@pytest.mark.parametrize("n,ratio,kind,bound", LONG + ROW)
+def test_layer_against_step(sc, n, ratio, kind, bound):
     torch, dev = torch_dev()
     K = 8
     G = gradients(torch, dev, kind, K, n)
@@ -62,4 +65,4 @@ def test_layer_against_step(sc, n, ratio, kind):
     layer = sc.LayerSelect(G, [0, n], [ratio] * K)
     t_layer = best_us(torch, layer.run)
     log(f"layer of {n}, ratio {ratio}, {kind}: {t_layer:.0f} us, step {t_step:.0f} us")
-    assert t_layer <= 1.3 * t_step
+    assert t_layer <= bound * t_step
