@@ -365,7 +365,7 @@ const char* scadles_last_error(void);
  *                       SCADLES_EINTERNAL if its internal checks failed;
  *                       scadles_topk_select_layers and
  *                       scadles_step_fused_layers do the same for their
- *                       layers of more than "row_max" elements (all of these
+ *                       layers that are not rows, see "row_max" (all of these
  *                       then synchronise `stream`).
  *   "inject_count_error" 1 (testing): the multi-launch selection (of the
  *                       whole vector, and of a per-layer selection's long
@@ -381,14 +381,15 @@ const char* scadles_last_error(void);
  *                       overlaps the end of group i-1's selection, which runs
  *                       on a second stream the library creates per GPU, at the
  *                       default priority). Results do not depend on it.
- *   "row_max"        0..2^32-1: in the per-layer selection, layers of at most
- *                       this many elements are selected as (device, layer)
- *                       rows; longer ones by the multi-launch selection,
- *                       consecutive ones pipelined on the library's second
- *                       stream and the rows on a third. Until it is set:
- *                       layers of up to 2^21 elements, and of up to 2^22 where
- *                       their rows can be split (see row_split) and few enough
- *                       entries are kept. Results do not depend on it.
+ *   "row_max"        -1..2^32-1 (default -1): in the per-layer selection,
+ *                       layers of at most this many elements are selected as
+ *                       (device, layer) rows; longer ones by the multi-launch
+ *                       selection, consecutive ones pipelined on the library's
+ *                       second stream and the rows on a third. -1: layers of
+ *                       up to 2^21 elements, and of up to 2^22 where their
+ *                       rows can be split (see row_split) and few enough
+ *                       entries are kept. The kept sets do not depend on it
+ *                       (the energies are summed in another order).
  *   "row_split"      0..2^32-1 (default 65536, the least that takes effect):
  *                       rows of more than this many elements (and at most
  *                       2^24) are read by one workgroup per 16384-element part

@@ -1269,7 +1269,7 @@ scadles_status scadles_set_option(const char* name, int64_t value)
   else if (!strcmp(name, "force_fallback")) g_force_fallback = value ? 1 : 0;
   else if (!strcmp(name, "inject_count_error")) g_inject_count_error = value ? 1 : 0;
   else if (!strcmp(name, "row_max")) {
-    if (value < 0 || value > 0xFFFFFFFFll) return fail(SCADLES_EINVAL, "row_max must be in [0, 2^32 - 1]");
+    if (value < kRowMaxAuto || value > 0xFFFFFFFFll) return fail(SCADLES_EINVAL, "row_max must be in [-1, 2^32 - 1]");
     g_row_max = value;
   }
   else if (!strcmp(name, "row_split")) {

@@ -116,6 +116,11 @@ def test_host_validation_before_any_launch(sc):
     assert sc._set_option(b"layer_order", -1) == E["inval"]
     for v in (0, 2, 1):
         assert sc._set_option(b"layer_order", v) == 0
+    # layers selected as rows: -1 (default) is the library's own rule, which can be set back
+    assert sc._set_option(b"row_max", -2) == E["inval"]
+    assert sc._set_option(b"row_max", 2**32) == E["inval"]
+    for v in (0, 2**32 - 1, -1):
+        assert sc._set_option(b"row_max", v) == 0
 
 
 def test_momentum_validation_before_any_launch(sc):

@@ -61,6 +61,6 @@ def test_energy_bits_independent_of_launch(sc, path):
         torch.cuda.synchronize()
         same("a layer of its own", sel.energies, "energies")
     finally:
-        sc.set_option("row_max", 1 << 21)
+        sc.set_option("row_max", -1)
         sc.set_option("parts", 1)
         sc.set_option("force_exact", 0)

@@ -1,6 +1,6 @@
-"""GPU tests of layers just above the size every layer is a row at, split into parts
-whose select workgroup holds the whole selection interval (the default rule;
-row_max is not set here), against the oracle, bit for bit."""
+"""GPU tests of layers just above the size every layer is a row at (the default
+rule, row_max -1) and of split rows whose values do not spread as a sample's would,
+against the oracle, bit for bit."""
 from __future__ import annotations
 
 import numpy as np
@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(scope="module")
 def sc():
     import paper_2301_08897_amd as m
+    m.set_option("row_max", -1)
     return m
 
 

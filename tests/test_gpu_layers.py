@@ -17,8 +17,10 @@ pytestmark = pytest.mark.gpu
 MODES = ("default", "force_exact", "force_fallback")
 # Layers of at most row_max elements are selected by one workgroup per
 # (device, layer) row; longer ones by the multi-launch selection. 0 sends every
-# layer to the multi-launch selection, 2^32 - 1 every layer to the rows.
-ROW_MAX_DEFAULT = 1 << 21
+# layer to the multi-launch selection, 2^32 - 1 every layer to the rows, and -1
+# (the default) takes layers up to 2^21 elements, and up to 2^22 where they suit, as rows.
+ROW_MAX_DEFAULT = -1
+ROW_LIMIT = 1 << 21
 ROW_MAXES = (ROW_MAX_DEFAULT, 0, 2**32 - 1)
 # Rows of more than row_split elements (at least 65536) are split into parts
 # read by workgroups of their own: the default splits every row above 65536
@@ -130,12 +132,12 @@ def test_layers_at_the_row_limit(sc):
     # bin too large for LDS), one just above it (multi-launch selection), and
     # a short tail
     rng = np.random.default_rng(15)
-    sizes = [ROW_MAX_DEFAULT, ROW_MAX_DEFAULT + 1, 3]
+    sizes = [ROW_LIMIT, ROW_LIMIT + 1, 3]
     seg_off = np.concatenate([[0], np.cumsum(sizes)]).tolist()
     G = rng.standard_normal((2, seg_off[-1])).astype(np.float32)
     log("layers at the row limit")
     layers_vs_oracle(sc, G, seg_off, [0.01, 0.3], "row limit", topk=oracle.topk_layers_by_threshold,
-                     row_maxes=(ROW_MAX_DEFAULT,))
+                     row_maxes=(ROW_MAX_DEFAULT, ROW_LIMIT))
 
 
 def test_rows_with_equal_keys(sc):
@@ -154,8 +156,8 @@ def test_rows_with_equal_keys(sc):
 def test_split_rows(sc):
     # rows split into parts: lengths around the part size (65536) and its
     # multiples, unaligned layer starts, a row whose keys are all equal and
-    # one with few magnitude levels (their selection intervals overflow, so
-    # the select kernel writes them on its own), dense large magnitudes in one
+    # one with few magnitude levels (their candidates overflow the list, so
+    # they are selected over all their elements), dense large magnitudes in one
     # part only
     rng = np.random.default_rng(18)
     sizes = [65_537, 3, 131_071, 131_073, 1, 200_000, 100_000, 90_001, 70_000]
@@ -450,6 +452,7 @@ def test_layers_validation_of_long_layers(sc):
     w, _ = sc.stream_weights([1.0, 2.0, 3.0])
     log("per-layer validation of the long layers' selection state")
     try:
+        sc.set_option("row_max", ROW_LIMIT)
         sc.set_option("validate", 1)
         sc.LayerSelect(G, seg_off, [0.01] * 3).run()
         sc.FusedStep(G, [0.01] * 3, seg_off=seg_off).run(w)
@@ -466,6 +469,7 @@ def test_layers_validation_of_long_layers(sc):
     finally:
         sc.set_option("inject_count_error", 0)
         sc.set_option("validate", 0)
+        sc.set_option("row_max", ROW_MAX_DEFAULT)
 
 
 def test_long_row_without_chunk_tallies(sc):
