@@ -30,7 +30,6 @@ __device__ inline f4 ld4(const GLOBAL float* p) { return *(const GLOBAL f4*)p; }
 __device__ inline f4 ld_stream4(const float* p) { return ld_stream4(gptr(p)); }
 __device__ inline f4 ld4(const float* p) { return ld4(gptr(p)); }
 #endif
-__device__ inline u4 ldu4(const uint32_t* p) { return *(const GLOBAL u4*)gptr(p); }
 
 // A device's gradient seen in a 16-byte-aligned "virtual" frame: real element i
 // sits at virtual position i + shift, shift = (address / 4) % 4, so every group

@@ -1,5 +1,5 @@
-// marks.h -- range markers of the weighted aggregation (device code shared by
-// the aggregation launch and the fused selection's decision launch).
+// marks.h -- range markers of the weighted aggregation: which devices have them,
+// and the search for sets that came from elsewhere.
 #pragma once
 
 #include "scadles_internal.h"

@@ -1,10 +1,11 @@
 // rows.hip -- per-layer Top-k of short layers (the per-layer reading of the
 // Top-k of §IV, ScaDLES arXiv 2301.08897): every (device, layer) row whose
-// layer has at most a few million elements is selected by one workgroup, all
-// such rows of all devices in one launch, instead of one multi-launch
-// selection per layer.
+// layer has at most a few million elements, all such rows of all devices in a few
+// launches, instead of one multi-launch selection per layer. Rows up to the
+// split threshold are selected by one workgroup each, longer ones by one
+// workgroup per part (see "split rows" below).
 //
-// Per row (31-bit magnitude keys, ties to the lower index): a systematic
+// Per unsplit row (31-bit magnitude keys, ties to the lower index): a systematic
 // sample brackets the k-th largest key; one read counts the keys above the
 // bracket, gathers the keys inside it into LDS and tallies every wave's chunk;
 // the exact key is selected among the gathered keys digit by digit (12 + 10 +

@@ -28,7 +28,6 @@ constexpr int kSegs = 16;              // list segments of the hot tiles per dev
 constexpr int kTicketSample = 0, kTicketRefine = 1, kTicketHist = 2, kTicketFull = 5, kTickets = 8;
 constexpr uint32_t kKeyInf = 0x80000000u;   // above every 31-bit key
 constexpr uint32_t kKeyMask = 0x7FFFFFFFu;
-constexpr uint64_t kSat31 = 0x7FFFFFFFull;
 constexpr int kFbRounds = 8;           // exact path's histogram blocks: rounds per block (at most: see Ctx::fb_rounds)
 constexpr int kFullWorkers = 1024;     // workgroups of the exact path's histogram passes
 constexpr int kHotWorkers = 4096;      // grid-stride workgroups for hot tiles
@@ -221,9 +220,9 @@ __device__ inline void momentum_step(float& p, float& v, float g, double nlr, do
 }
 
 // ---- per-layer selection of short layers: one workgroup per (device, layer) row ------
-// Layers of at most RowsCtx::row_max elements are selected by k_rows, one
-// workgroup of kRowBlock threads per row, instead of running the multi-launch
-// selection once per layer.
+// The layers that row_layer (api.hip) takes as rows are selected by k_rows, one
+// workgroup of kRowBlock threads per row, or, when they are long, part by part
+// (below), instead of running the multi-launch selection once per layer.
 constexpr int kRowBlock = 1024;
 constexpr int kRowCand = 14336;        // keys of the threshold bin held in LDS
 constexpr int kPutWords = 200;         // table words per k_put launch (kernel-argument copy)

@@ -30,7 +30,6 @@
 // decision) are done by the last workgroup of the launch whose results they
 // need, not by a launch of their own: see block_is_last.
 #include "frame.h"
-#include "marks.h"
 #include "radix.h"
 
 namespace scadles {
@@ -223,11 +222,6 @@ __global__ __launch_bounds__(kBlock) void k_refine(Ctx c)
 // them; a hot tile appends the latter to one of the device's list segments
 // (in turn, so that the appends do not queue on one address). Only hot tiles
 // use atomics: one per tile cost this pass 2% (30 x 143.7M: 2.63 -> 2.68 ms).
-template <int R>
-__device__ inline uint64_t elem_of(uint32_t w, int r, uint32_t l)
-{
-  return (uint64_t)w * (R * 256) + (uint64_t)r * 256 + l * 4;
-}
 
 // One round of phase 1 for one wave: sum of squares, counts of candidates
 // (key >= tlo) and sure keys (key >= thi), and the round's candidates staged in
