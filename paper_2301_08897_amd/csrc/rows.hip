@@ -312,16 +312,20 @@ __device__ inline uint32_t row_select_global(const Row& row, uint64_t vend, uint
 // chunks every kRowSampleStride elements; the whole row when it is short):
 // the bins of its 13-bit histogram (in shist, kRowCand words of LDS) around
 // k's expected sample rank, six standard deviations and 8 ranks either side.
-// With `refine` a second pass over the sample tells apart kRowRefineBits more
-// bits within the two bins: a long row's bins of 3% of the magnitude may hold
-// more keys than its select workgroup has room for.
+// For a split row (kSplit) a second pass over the sample tells apart
+// kRowRefineBits more bits within the two bins: a long row's bins of 3% of the
+// magnitude may hold more keys than its select workgroup has room for. Its
+// sample is also read with more in flight and its equal keys counted together;
+// for the others, mostly less than a round of the workgroup, that costs more than it
+// gives (64 x 400 layers of 5000: 2.70 ms against 2.45).
 constexpr int kRowRefineBits = 11;
-__device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t vend, bool refine, uint32_t* shist,
-                                   uint32_t* s_w, uint32_t* s_res, uint32_t& t_lo, uint32_t& t_hi)
+template <bool kSplit>
+__device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t vend, uint32_t* shist, uint32_t* s_w,
+                                   uint32_t* s_res, uint32_t& t_lo, uint32_t& t_hi)
 {
   static_assert((1 << kRowSampleBits) <= kRowCand, "the sample histogram fits the candidate array");
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-  const bool whole = d.n <= (uint32_t)kRowWholeMax;
+  const bool whole = !kSplit && d.n <= (uint32_t)kRowWholeMax;
   const uint64_t stride = whole ? 256u : (uint64_t)kRowSampleStride;
   for (uint32_t i = tid; i < (1u << kRowSampleBits); i += kRowBlock) shist[i] = 0u;
   __syncthreads();
@@ -370,7 +374,28 @@ __device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t ve
   };
   constexpr int kShift = 31 - kRowSampleBits;
   const SelView all{0u, kKeyInf, (uint32_t)kShift, (uint32_t)kRowSampleBits, 0u};
-  sample([&](const uint32_t (&key)[16], uint32_t valid) { count_digits<true>(all, key, valid, shist); });
+  if (kSplit) {
+    sample([&](const uint32_t (&key)[16], uint32_t valid) { count_digits<true>(all, key, valid, shist); });
+  } else {
+    for (uint64_t c0 = w; c0 * stride < vend; c0 += 4 * kRowWaves) {
+      f4 x[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint64_t v = (c0 + r * kRowWaves) * stride + 4u * lane;
+        x[r] = v < vend ? load4(row, v, false) : f4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint64_t v = (c0 + r * kRowWaves) * stride + 4u * lane;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (v < vend && in_row(row, v + q)) {
+            atomicAdd(&shist[key_of(x[r][q]) >> kShift], 1u);
+            ++s_cnt;
+          }
+      }
+    }
+  }
   uint32_t s_n;
   row_scan(s_cnt, s_w, s_n);
   // sample ranks bracketing the k-th largest key
@@ -398,7 +423,7 @@ __device__ inline void row_bracket(const RowDesc& d, const Row& row, uint64_t ve
   }
   t_lo = lo << kShift;
   t_hi = r_hi >= 1 ? (hi + 1u) << kShift : kKeyInf;
-  if (!refine || whole) return;
+  if (!kSplit) return;
   constexpr int kFine = kShift - kRowRefineBits;
   constexpr uint32_t kN = 1u << kRowRefineBits;
   static_assert(2 * kN <= kRowCand, "both bins' finer histograms fit the candidate array");
@@ -493,7 +518,10 @@ __device__ inline double row_write_ordered(const RowDesc& d, const Row& row, uin
 // at or above t_hi, gathers the keys inside the bracket into LDS and sums g^2;
 // the k-th largest key is selected among the gathered ones. If the bracket
 // missed or overflowed LDS, the digits are decided over the whole row instead.
-// A last read writes the kept entries in index order.
+// A last read writes the kept entries in index order. kSplit: there are split rows
+// (without them the kernel needs fewer registers: 64 x 400 layers of 5000, 2.44 ms
+// per step against 2.50).
+template <bool kSplit>
 __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
 {
   __shared__ uint32_t hist[kRowBins];
@@ -509,8 +537,8 @@ __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
 
   // 1. bracket from the sample; that is all a split row needs here
   uint32_t t_lo, t_hi;
-  row_bracket(d, row, vend, blockIdx.x < rc.Lb * rc.K, cand, s_w, s_res, t_lo, t_hi);
-  if (blockIdx.x < rc.Lb * rc.K) {
+  if (kSplit && blockIdx.x < rc.Lb * rc.K) {
+    row_bracket<true>(d, row, vend, cand, s_w, s_res, t_lo, t_hi);
     for (uint32_t i = tid; i < (uint32_t)kBins; i += kRowBlock) rc.slow_hist[(uint64_t)blockIdx.x * kBins + i] = 0u;
     if (tid == 0) {
       BigRowState st;
@@ -523,6 +551,7 @@ __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
     }
     return;
   }
+  row_bracket<false>(d, row, vend, cand, s_w, s_res, t_lo, t_hi);
 
   // 2. one read: keys >= t_hi counted, keys in [t_lo, t_hi) gathered, sum g^2
   if (tid == 0) s_res[3] = 0u;
@@ -1447,7 +1476,8 @@ hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* ta
   }
   if (count > kPutWords) a.count = 0;
   k_rows_prep<<<rc.K, 256, 0, s>>>(rc, rp, a);
-  if (rc.Ls > 0) k_rows<<<rc.Ls * rc.K, kRowBlock, 0, s>>>(rc);
+  if (rc.Lb > 0) k_rows<true><<<rc.Ls * rc.K, kRowBlock, 0, s>>>(rc);
+  else if (rc.Ls > 0) k_rows<false><<<rc.Ls * rc.K, kRowBlock, 0, s>>>(rc);
   if (rc.Lb > 0) {
     k_big_gather<<<rc.nparts, kPartBlock, 0, s>>>(rc);
     k_big_select<<<rc.Lb * rc.K, kRowBlock, 0, s>>>(rc);
