@@ -252,9 +252,12 @@ bool make_layout(uint32_t K, uint64_t n, const double* ratios, bool force_exact,
     }
   }
   // Blocks of the exact path's histogram passes: kFbRounds rounds, fewer where
-  // that leaves compute units without one.
+  // that leaves most compute units without one. (Each block's workgroup flushes a
+  // histogram, so more of them cost more than they spread: one of 1 M at ratio 0.5
+  // 96, 79, 70 and 67 us with at least 512, 256, 128 and 64 blocks; 4 x 61,706 of
+  // mostly zeros 62, 64, 63 and 68.)
   L.fb_rounds = kFbRounds;
-  while (L.fb_rounds > 1 && (uint64_t)K * ceil_div_u64(n + 3, (uint64_t)L.fb_rounds * kRound) < 512) L.fb_rounds /= 2;
+  while (L.fb_rounds > 1 && (uint64_t)K * ceil_div_u64(n + 3, (uint64_t)L.fb_rounds * kRound) < 128) L.fb_rounds /= 2;
   L.nfb = ceil_div_u64(n + 3, (uint64_t)L.fb_rounds * kRound);
   size_t o = 0;
   auto take = [&](size_t bytes) {

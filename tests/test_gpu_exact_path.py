@@ -1,5 +1,5 @@
 """GPU tests of the exact path's digit passes against the oracle, bit for bit, at
-sizes where their blocks are whole (at least 512 blocks of 8192 elements) and just
+sizes where their blocks are whole (at least 128 blocks of 8192 elements) and just
 below: values all different, mostly zeros and tied, which are counted in different
 ways, at every 4-byte offset; devices on the exact path beside sampled ones."""
 from __future__ import annotations
@@ -30,8 +30,8 @@ def values(rng, kind, n):
     return x
 
 
-# eight devices: 64 blocks each from n = 63 * 8192 - 2 on
-@pytest.mark.parametrize("n", [63 * 8192 - 3, 63 * 8192 + 1, 64 * 8192 - 3])
+# eight devices: 16 blocks each from n = 15 * 8192 - 2 on
+@pytest.mark.parametrize("n", [15 * 8192 - 3, 15 * 8192 + 1, 16 * 8192 - 3, 63 * 8192 + 1])
 @pytest.mark.parametrize("kind", ["normal", "zeros", "ties", "runs", "mixed"])
 def test_exact_path(sc, n, kind):
     log(f"exact path n={n} {kind}")
