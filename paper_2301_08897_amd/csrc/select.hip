@@ -1333,15 +1333,16 @@ static void launch_post(const Ctx& c, const SelectPlan& p, hipStream_t s, int ha
   };
   // A hot tile's time is its workgroup's: 16 waves where a few tiles are all
   // there is (4 x 61,706: 11.5 us against 17), 8 where they sum their own offsets
-  // (8 x 11.2 M: 34 against 40) or are at most 4096 in all (one of 25.6 M, 1560
-  // tiles: 134 us per step against 138), else 4 (2 x 60.2 M, 7348 tiles: 279 against
-  // 282; 16 x 25.6 M at ratio 0.1: 725 against 739), also beside a main pass, which
-  // rarely leaves 8 free at once (per-layer step of 16 x 143.7 M: 2680 against 2754).
+  // (8 x 11.2 M: 34 against 40) or are at most 16384 in all (one of 143.7 M whose
+  // entries lie in few layers, 8769 tiles: 14 against 20; with the entries spread,
+  // 502 us per step with 4, 505 with 8), else 4 (16 x 25.6 M at ratio 0.1, 24960
+  // tiles: 725 us per step against 739), also beside a main pass, which rarely
+  // leaves 8 free at once (per-layer step of 16 x 143.7 M: 2680 against 2754).
   const uint64_t tiles = (uint64_t)c.jn * c.nslot;
   if (own_offsets(c, p)) {
     if (tiles <= 512) write(k_write<1024, true>, 1024);
     else write(k_write<512, true>, 512);
-  } else if (tiles <= 4096 && !p.beside) {
+  } else if (tiles <= 16384 && !p.beside) {
     write(k_write<512, false>, 512);
   } else {
     write(k_write<256, false>, 256);

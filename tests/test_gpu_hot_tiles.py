@@ -70,8 +70,8 @@ def test_tied_run(sc, K, shift, start, length):
 
 
 # more than 1024 tiles per device: offsets from a launch of their own, for 512-thread
-# workgroups and, with more than 4096 tiles in all, 256-thread ones
-@pytest.mark.parametrize("K,shift", [(1, 1), (1, 3), (4, 3)])
+# workgroups and, with more than 16384 tiles in all, 256-thread ones
+@pytest.mark.parametrize("K,shift", [(1, 1), (1, 3), (16, 3)])
 def test_tied_run_of_many_tiles(sc, K, shift):
     log(f"hot tiles: {K} devices of 1025 tiles, offset {shift}")
     n = 1024 * TILE + 3
