@@ -833,7 +833,9 @@ static scadles_status run_layers(const float* const* grads, uint32_t K, const ui
     if (e == hipSuccess) e = hipStreamWaitEvent(sr, ss->fork, 0);
     if (e != hipSuccess) return hip_fail(e, "row stream fork");
   }
-  e = launch_rows(rc, rp, table.data(), table.size(), any_long ? nullptr : energies, sr);
+  // the split rows come longest first
+  const uint64_t longest = Lb ? seg_off[shorts[0] + 1] - seg_off[shorts[0]] : 0;
+  e = launch_rows(rc, rp, table.data(), table.size(), longest, any_long ? nullptr : energies, sr);
   if (e != hipSuccess) return hip_fail(e, "row selection");
   if (rows_beside) {
     e = hipEventRecord(ss->rows_done, sr);

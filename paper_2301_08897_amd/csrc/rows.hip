@@ -721,7 +721,8 @@ __global__ __launch_bounds__(kRowBlock) void k_rows(RowsCtx rc)
 //                  the slow rows, by all of the GPU: three digit passes over the
 //                  rows' elements, the chunks' counts and prefixes, the output,
 //                  all read from the gradient. Without slow rows these end at once
-//                  (five launches of 4.5 us);
+//                  (five launches of 4.5 us); where every split row is short,
+//                  k_slow_rows takes them instead;
 //   k_rows_energy  the energies of each row from its waves' sums, in order, then
 //                  the device's.
 // No workgroup waits for another inside a launch, and the gather has no
@@ -1405,6 +1406,36 @@ __global__ __launch_bounds__(kBlock) void k_slow_write(RowsCtx rc)
       [](const SlowRow&, uint32_t) {});
 }
 
+// The slow rows where all split rows are short: one workgroup each, in one launch
+// instead of five (of 4.5 us each without slow rows; 3 x 75 layers of 311 k in all
+// take 70 us so, 77 with the passes).
+constexpr uint32_t kSlowOneMax = 1u << 18;      // longest row of these
+constexpr uint32_t kSlowOneWorkers = 256;
+__global__ __launch_bounds__(kRowBlock) void k_slow_rows(RowsCtx rc)
+{
+  __shared__ uint32_t hist[kRowBins];
+  __shared__ uint32_t cand[kRowCand];
+  __shared__ uint32_t s_w[kRowWaves];
+  __shared__ uint32_t s_res[4];
+  __shared__ double s_d[kRowWaves];
+  const uint32_t n = (uint32_t)(*rc.slow_cnt >> 32);
+  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const uint32_t b = rc.slow_list[2 * i];
+    const RowDesc d = rc.rows[b];
+    uint32_t g0, np;
+    row_parts(rc, b, g0, np);
+    const Row row{gptr(d.grad), ((uint64_t)d.grad >> 2) & 3u, d.n};
+    const uint64_t vend = (uint64_t)d.n + row.shift;
+    uint32_t need = d.k;
+    const uint32_t thr = row_select_global(row, vend, need, hist, cand, s_w, s_res);
+    const double ek =
+        row_sum_f64(row_write_ordered(d, row, vend, thr, need, gptr(d.idx_out), gptr(d.val_out), s_w), s_d);
+    double* e = rc.part_e + ((uint64_t)rc.nparts + g0) * kPartWaves;
+    for (uint32_t q = threadIdx.x; q < np * kPartWaves; q += kRowBlock) e[q] = q == 0 ? ek : 0.0;
+    __syncthreads();
+  }
+}
+
 // Per device: the energies of its split rows (a wave per row), then the
 // energies of all its layers, short and long (each lane a strided subset in
 // layer order, then the lanes in a fixed tree).
@@ -1462,8 +1493,8 @@ hipError_t launch_layers_decide(const DecideArgs& a, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* table, uint64_t count, double* energies,
-                       hipStream_t s)
+hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* table, uint64_t count, uint64_t longest,
+                       double* energies, hipStream_t s)
 {
   uint64_t* dst = const_cast<uint64_t*>(rc.table);
   PutArgs a;
@@ -1482,10 +1513,15 @@ hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* ta
     k_big_gather<<<rc.nparts, kPartBlock, 0, s>>>(rc);
     k_big_select<<<rc.Lb * rc.K, kRowBlock, 0, s>>>(rc);
     k_big_write<<<rc.nparts, kPartBlock, 0, s>>>(rc);
-    const uint32_t workers = rc.nparts < kSlowWorkers ? rc.nparts : kSlowWorkers;
-    for (uint32_t pass = 0; pass < kSlowPasses; ++pass) k_slow_hist<<<workers, kBlock, 0, s>>>(rc, pass);
-    k_slow_count<<<workers, kBlock, 0, s>>>(rc);
-    k_slow_write<<<workers, kBlock, 0, s>>>(rc);
+    if (longest <= kSlowOneMax) {
+      const uint32_t rows = rc.Lb * rc.K;
+      k_slow_rows<<<rows < kSlowOneWorkers ? rows : kSlowOneWorkers, kRowBlock, 0, s>>>(rc);
+    } else {
+      const uint32_t workers = rc.nparts < kSlowWorkers ? rc.nparts : kSlowWorkers;
+      for (uint32_t pass = 0; pass < kSlowPasses; ++pass) k_slow_hist<<<workers, kBlock, 0, s>>>(rc, pass);
+      k_slow_count<<<workers, kBlock, 0, s>>>(rc);
+      k_slow_write<<<workers, kBlock, 0, s>>>(rc);
+    }
   }
   if (rc.Ls > 0 && energies) k_rows_energy<<<rc.K, kEnergyBlock, 0, s>>>(rc, energies);
   return hipGetLastError();

@@ -322,8 +322,9 @@ struct DecideArgs {
 hipError_t launch_layers_decide(const DecideArgs& a, hipStream_t s);
 // Table (copied to rc.table), preparation and selection of the short layers' rows;
 // energies (null: launch_rows_energy follows later) = all layers' sums per device.
-hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* table, uint64_t count, double* energies,
-                       hipStream_t s);
+// longest: elements of the longest split row.
+hipError_t launch_rows(const RowsCtx& rc, const RowsPrep& rp, const uint64_t* table, uint64_t count, uint64_t longest,
+                       double* energies, hipStream_t s);
 hipError_t launch_rows_energy(const RowsCtx& rc, double* energies, hipStream_t s);
 hipError_t launch_zero_words(uint32_t* p, uint32_t n, hipStream_t s);
 

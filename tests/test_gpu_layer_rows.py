@@ -72,19 +72,21 @@ def uneven(rng, kind, n, ratio):
     return x.astype(np.float32)
 
 
+# (the last set: split rows short enough for a workgroup each when they are slow)
 @pytest.mark.parametrize("ratio", [0.02, 0.001])
-@pytest.mark.parametrize("kinds", [(k,) * 2 for k in KINDS] + [KINDS + ("normal",)])
-def test_uneven_rows(sc, ratio, kinds):
-    log(f"uneven layer rows: ratio {ratio}, {kinds}")
+@pytest.mark.parametrize("kinds,sizes", [((k,) * 2, SIZES) for k in KINDS] + [(KINDS + ("normal",), SIZES)]
+                         + [(KINDS + ("normal",), (200_001,) + SIZES[3:])])
+def test_uneven_rows(sc, ratio, kinds, sizes):
+    log(f"uneven layer rows: ratio {ratio}, {kinds}, {len(sizes)} layers")
     torch, dev = torch_dev()
-    seg_off = np.concatenate([[0], np.cumsum(SIZES)]).astype(np.int64)
+    seg_off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
     n, K = int(seg_off[-1]), len(kinds)
     rng = np.random.default_rng(K)
     room = torch.zeros(K, n + 4, dtype=torch.float32, device=dev)
     G = np.empty((K, n), dtype=np.float32)
     for j, kind in enumerate(kinds):
         G[j] = np.concatenate([uneven(rng, kind, m, ratio) if kind != "normal" else
-                               rng.standard_normal(m).astype(np.float32) for m in SIZES])
+                               rng.standard_normal(m).astype(np.float32) for m in sizes])
         room[j, j % 4:j % 4 + n].copy_(torch.from_numpy(G[j]))
     sel = sc.LayerSelect([room[j, j % 4:j % 4 + n] for j in range(K)], seg_off, [ratio] * K)
     for again in range(2):                    # the second call finds the first one's workspace
